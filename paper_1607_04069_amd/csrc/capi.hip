@@ -784,6 +784,24 @@ pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, hi
   t.first_atom = src->first_atom;
   t.seed = src->seed;
   t.job = src->job_id;
+  t.f.L = (float)t.L;
+  t.f.inv_L = (float)(1.0 / t.L);
+  t.f.inv_nu = (float)t.inv_nu_max;
+  t.f.sig_gas = (float)t.sig_gas;
+  t.f.m_ratio = (float)t.m_ratio;
+  t.f.M_ratio = (float)t.M_ratio;
+  t.f.sg_exp = (float)t.sg_exp;
+  t.f.log2_gcap = (float)t.log2_gcap;
+  t.f.dt = (float)t.dt;
+  t.f.nu_dt = (float)t.nu_dt;
+  t.f.xbin = (float)t.xbin;
+  t.f.inv_xbin = (float)t.inv_xbin;
+  t.f.s_max = (float)t.s_max;
+  t.f.u_s = (float)t.u_s;
+  t.f.v_per_sqrt_ev = (float)t.v_per_sqrt_ev;
+  t.f.e_half_m = (float)t.e_half_m;
+  t.f.ebin = (float)t.ebin;
+  t.f.tbin = (float)t.tbin;
   const TpLayout L = tp_layout(tp);
   pm::TpTally* tal = reinterpret_cast<pm::TpTally*>(base + L.tally);
   uint64_t* eh = reinterpret_cast<uint64_t*>(base + L.e_hist);
@@ -804,9 +822,7 @@ pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, hi
     tr.vy = out->trace->vy;
     tr.vz = out->trace->vz;
   }
-  const int64_t want = (src->n_atoms + pm::kBlock - 1) / pm::kBlock;
-  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(want, 256 * 8));
-  if (src->n_atoms > 0) PM_TRY(pm::launch_tp_flight(t, tal, eh, th, tofh, tr, prof, grid, st));
+  if (src->n_atoms > 0) PM_TRY(pm::launch_tp_flight(t, tal, eh, th, tofh, tr, prof, st));
   const int nx = t.n_xbins;
   if (nx) {
     const double per_atom = src->flux_m2s / (double)std::max<int64_t>(src->n_atoms, 1);
@@ -826,13 +842,13 @@ pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, hi
     }
   PM_TRY(hipStreamSynchronize(st));
   out->n_substrate = (int64_t)h.n_sub;
-  out->n_target = (int64_t)h.n_tgt;
+  out->n_target = src->n_atoms - (int64_t)h.n_sub - (int64_t)h.n_unf;
   out->n_unfinished = (int64_t)h.n_unf;
-  out->events = h.events;
-  out->collisions = h.collisions;
+  out->events = h.sum[2];
+  out->collisions = h.sum[3];
   out->overflow = h.overflow;
-  out->e_sum_substrate = (double)h.e_sub_fx / 1048576.0;
-  out->e_sum_target = (double)h.e_tgt_fx / 1048576.0;
+  out->e_sum_substrate = (double)(int64_t)h.sum[1] / 1048576.0;
+  out->e_sum_target = (double)(int64_t)h.sum[0] / 1048576.0;
   out->eta = src->n_atoms > 0 ? (double)h.n_sub / (double)src->n_atoms : 0.0;
   out->deposition_flux = out->eta * src->flux_m2s;
   out->nu_max = t.nu_max;

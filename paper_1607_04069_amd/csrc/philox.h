@@ -39,6 +39,15 @@ __device__ __forceinline__ void mulhilo64(uint64_t a, uint64_t b, uint64_t& hi, 
   hi = a1 * b1 + (t >> 32) + (u >> 32);
 }
 
+// a ^ b ^ c per word by the three-input bitwise operation (0x96: the sum of the
+// three bits): two instructions for the 64-bit exclusive ors of a round's half
+// instead of four.
+__device__ __forceinline__ uint64_t xor3(uint64_t a, uint64_t b, uint64_t c) {
+  const uint32_t lo = __builtin_amdgcn_bitop3_b32((uint32_t)a, (uint32_t)b, (uint32_t)c, 0x96);
+  const uint32_t hi = __builtin_amdgcn_bitop3_b32((uint32_t)(a >> 32), (uint32_t)(b >> 32), (uint32_t)(c >> 32), 0x96);
+  return (uint64_t)hi << 32 | lo;
+}
+
 __device__ __forceinline__ Words4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3,
                                                 uint64_t k0, uint64_t k1) {
   const uint64_t MA = 0xD2E7470EE14C6C93ull, MB = 0xCA5A826395121157ull;
@@ -48,22 +57,29 @@ __device__ __forceinline__ Words4 philox4x64_10(uint64_t c0, uint64_t c1, uint64
     uint64_t pa_hi, pa_lo, pb_hi, pb_lo;
     mulhilo64(MA, c0, pa_hi, pa_lo);
     mulhilo64(MB, c2, pb_hi, pb_lo);
-    const uint64_t n0 = pb_hi ^ c1 ^ k0;
-    const uint64_t n2 = pa_hi ^ c3 ^ k1;
+    const uint64_t n0 = xor3(pb_hi, c1, k0);
+    const uint64_t n2 = xor3(pa_hi, c3, k1);
     c0 = n0; c1 = pb_lo; c2 = n2; c3 = pa_lo;
     k0 += KA; k1 += KB;
   }
   return Words4{c0, c1, c2, c3};
 }
 
+// (m + 0.5) 2^-23 of the upper 23 bits m of a 32-bit word: in FP32 the bits
+// become the mantissa of a number in [1, 2) (one shift of two words joined) and
+// 1 - 2^-24 is taken off, which is exact; two instructions where the conversion,
+// sum and product take four.
 template <typename R>
-__device__ __forceinline__ R u_hi(uint64_t w) {
-  return ((R)(uint32_t)(w >> 41) + (R)0.5) * (R)1.1920928955078125e-07;   // 2^-23
+__device__ __forceinline__ R u_23(uint32_t v) {
+  if constexpr (sizeof(R) == 4)
+    return __uint_as_float(0x3F800000u | v >> 9) - 0.999999940395355224609375f;
+  else
+    return ((R)(v >> 9) + (R)0.5) * (R)1.1920928955078125e-07;   // 2^-23
 }
 template <typename R>
-__device__ __forceinline__ R u_lo(uint64_t w) {
-  return ((R)(uint32_t)((w >> 9) & 0x7FFFFFu) + (R)0.5) * (R)1.1920928955078125e-07;
-}
+__device__ __forceinline__ R u_hi(uint64_t w) { return u_23<R>((uint32_t)(w >> 32)); }
+template <typename R>
+__device__ __forceinline__ R u_lo(uint64_t w) { return u_23<R>((uint32_t)w); }
 
 // The 8 uniforms of one call.
 template <typename R>

@@ -34,7 +34,15 @@ hipError_t launch_scan_cells(const CaseConst&, const GridPtrs&, Ctrl*, hipStream
 hipError_t launch_diag_reset(const CaseConst&, const GridPtrs&, Ctrl*, hipStream_t);
 
 // sputter yield and test-particle flight
+
+// The flight's constants in its own precision (in registers, not converted there).
+struct TpFloat {
+  float L, inv_L, inv_nu, sig_gas, m_ratio, M_ratio, sg_exp, log2_gcap, dt, nu_dt, xbin, inv_xbin, s_max, u_s,
+      v_per_sqrt_ev, e_half_m, ebin, tbin;
+};
+
 struct TpConst {
+  TpFloat f;
   double L, lat;
   double nu_max;             // n_gas (sigma g)_max
   double inv_nu_max;
@@ -57,13 +65,17 @@ struct TpConst {
   int64_t e_max;
   int64_t n_atoms, first_atom;
   uint64_t seed, job;
+  int wlog;                  // lanes per atom at the start: 2^wlog (set by the launcher)
+  int64_t run, first_run;    // atoms a wavefront takes at a time; the first run that is no wavefront's own
 };
 
 struct TpTally {              // device tallies (zeroed before a run)
-  uint64_t n_sub, n_tgt, n_unf;
-  uint64_t events, collisions, overflow;
-  int64_t e_sub_fx, e_tgt_fx;  // energy sums, units of 2^-20 eV
-  uint64_t pad[8];
+  uint64_t sum[4];             // impact energies at the target, at the substrate (2^-20 eV), events, collisions
+  uint64_t n_sub, n_unf;       // the other atoms ended at the target
+  uint64_t overflow;
+  uint64_t pad0[9];
+  uint64_t next;               // atoms taken by the flight's wavefronts beyond their first runs
+  uint64_t pad1[15];
 };
 
 struct TpTrace {
@@ -80,8 +92,8 @@ struct TpTrace {
 // prof: [4][n_xbins + 1] int64 track-length tallies (partial-cell times, full-cell
 // time differences, partial-cell displacements, full-cell displacement
 // differences), or null
-hipError_t launch_tp_flight(const TpConst&, TpTally* tally, uint64_t* e_hist, uint64_t* th_hist,
-                            uint64_t* tof_hist, TpTrace trace, int64_t* prof, int grid, hipStream_t);
+hipError_t launch_tp_flight(TpConst, TpTally* tally, uint64_t* e_hist, uint64_t* th_hist, uint64_t* tof_hist,
+                            TpTrace trace, int64_t* prof, hipStream_t);
 // track-length tallies -> [4][nx] doubles: time (s), displacement (m), density (m^-3), mean v_x (m/s)
 hipError_t launch_tp_profiles(const int64_t* prof, int nx, double h, double per_atom, double* out, hipStream_t st);
 hipError_t launch_zero_u64(void* p, size_t bytes, hipStream_t st);
