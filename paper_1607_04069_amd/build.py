@@ -24,6 +24,11 @@ ARCH = os.environ.get("PM_OFFLOAD_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # the loops of these kernels run a few times and hold FP64 logarithms, whose
+         # constants the compiler would keep in registers throughout: k_step needs 62
+         # VGPRs instead of 80 and scratch, k_mcc 75 instead of 97 (the 64-discharge
+         # sweep: 356 ms for 4 RF periods instead of 376)
+         "-mllvm", "-disable-machine-licm",
          "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
