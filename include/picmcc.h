@@ -410,7 +410,7 @@ pm_status pm_case_info(const pm_case* c, double* dx, double* dt, double* weight,
 
 /* Per-workgroup timestamps of the last step when the environment variable
  * PM_PROFILE=1 was set at pm_init_case, in the 100 MHz device wall clock.  A
- * step is two launches.  Push workgroup g writes out[8*g + k]: its start (k=0),
+ * step of such a case is two launches.  Push workgroup g writes out[8*g + k]: its start (k=0),
  * after staging the field (k=1), after its particle loop (k=2), after listing
  * its collision candidates (k=3) and at its end, after the charge flush (k=4).
  * Collision workgroup g writes its start (k=5), the end of its collisions
@@ -424,7 +424,9 @@ pm_status pm_get_step_profile(pm_case* c, uint64_t* out, int64_t cap, int32_t* g
  * How the step kernels (push, collisions, sort) are launched.  The shape changes
  * speed only: every shape computes the same particles (by id), charges and
  * diagnostics, because the random numbers depend on (seed, case_id, particle
- * id, step) and the charge sums are integers. */
+ * id, step) and the charge sums are integers.  unroll, waves and work_groups
+ * shape the push launch of a batch or of a single step of a case; several steps
+ * of a case in one call choose their own grid. */
 typedef struct {
   int32_t unroll;         /* particles per lane in flight: 8 or 16                      */
   int32_t waves;          /* register budget of the push kernel: 0 the compiler's own,  */
@@ -543,7 +545,8 @@ pm_status pm_batch_set_slot(pm_batch* b, int32_t slot, pm_case* c, void* hip_str
 
 /* --- measurement --------------------------------------------------------------
  * Advance n_steps steps with plain launches (the sorting schedule of pm_step),
- * bracketing every push and collision launch with HIP events on the stream it
+ * each as a push and a collision launch, which is how a batch and a single step
+ * of a case run (several steps of a case take one launch each), bracketing every push and collision launch with HIP events on the stream it
  * runs on, and return the average duration of each kind of launch in ms.  A
  * batch runs its lanes one after another here, so each launch has the device
  * to itself.  Synchronises. */

@@ -26,6 +26,8 @@ namespace pm {
 // ------------------------------------------------------------------ helpers
 __device__ __forceinline__ float dsqrt(float x) { return sqrtf(x); }
 __device__ __forceinline__ double dsqrt(double x) { return sqrt(x); }
+__device__ __forceinline__ float dfma(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double dfma(double a, double b, double c) { return fma(a, b, c); }
 __device__ __forceinline__ float dlog(float x) { return logf(x); }
 __device__ __forceinline__ double dlog(double x) { return log(x); }
 __device__ __forceinline__ float dacos(float x) { return acosf(x); }
@@ -99,6 +101,10 @@ __device__ __forceinline__ double drive_voltage(const CaseConst& c, int64_t step
   return c.V0 * cos(wt + c.phase) + c.V2 * cos(2.0 * wt + c.phase2);
 }
 
+__device__ __forceinline__ FusedNext fused_next(const CaseConst& c, int64_t l) {
+  return FusedNext{drive_voltage(c, l), (int)(l % 3), c.n_phase > 0 ? phase_bin(c, l) : -1};
+}
+
 __device__ __forceinline__ void add128(uint64_t* acc, int64_t v) {
   const uint64_t lo = acc[0];
   const uint64_t nlo = lo + (uint64_t)v;
@@ -117,14 +123,15 @@ __device__ __forceinline__ T wave_incl_scan(T v, int lane) {
   return v;
 }
 
-// Inclusive scan over the 256 threads of a workgroup; *total receives the sum.
-// s_w is 4 entries of LDS.  The combination order is fixed, so FP64 results are
-// reproducible run to run.
+// Inclusive scan over the first 256 threads of a workgroup; *total receives the
+// sum (all threads call it).  s_w is 4 entries of LDS.  The combination order is
+// fixed, so FP64 results are reproducible run to run and the same in workgroups
+// of any width.
 template <typename T>
 __device__ __forceinline__ T block_incl_scan(T v, T* s_w, T* total) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const T x = wave_incl_scan(v, lane);
-  if (lane == 63) s_w[w] = x;
+  if (lane == 63 && w < kBlock / 64) s_w[w] = x;
   __syncthreads();
   T off = 0, tot = 0;
 #pragma unroll
@@ -232,8 +239,8 @@ __device__ void solve_field(const CaseConst& c, Load qload, double V, double* sE
 // interpolated value by kpush[s] / kpush[0] (1 for electrons).
 template <typename R>
 __device__ void publish_field(const CaseConst& c, const double* sE, Pair<R>* Epair, double* E64) {
-  const int N = c.N;
-  for (int j = threadIdx.x; j < N; j += kBlock) {
+  const int N = c.N, width = blockDim.x;
+  for (int j = threadIdx.x; j < N; j += width) {
     const double e0 = sE[j], e1 = sE[j + 1];
     Pair<R> pr;
     pr.a = (R)(c.kpush[0] * e0);
@@ -241,7 +248,7 @@ __device__ void publish_field(const CaseConst& c, const double* sE, Pair<R>* Epa
     Epair[j] = pr;
   }
   if (E64)
-    for (int m = threadIdx.x; m <= N; m += kBlock) E64[m] = sE[m];
+    for (int m = threadIdx.x; m <= N; m += width) E64[m] = sE[m];
 }
 
 // LDS working set of the field solve, carved from a raw buffer of
@@ -668,6 +675,26 @@ __device__ __forceinline__ void flush_counters(Ctrl* C, CtrBank* B, const uint32
   }
 }
 
+// The same by one lane per counter; the net charge goes to *net.
+__device__ __forceinline__ void fused_counters(Ctrl* C, CtrBank* B, const uint32_t* cn, int64_t* net) {
+  const int k = threadIdx.x;
+  if (k >= CN_N) return;
+  // the bank's words in the order of the workgroup's counters (-1: none)
+  constexpr int8_t kWord[CN_N] = {0, 1, 2, 3, 4, 5, 7, 8, 9, 11, 12, 13, 14, 10, 10, -1};
+  uint64_t* to = reinterpret_cast<uint64_t*>(B) + kWord[k];
+  const int64_t abs_e0 = cn[CN_ABS], abs_e1 = cn[CN_ABS + 1], abs_i0 = cn[CN_ABS + 2], abs_i1 = cn[CN_ABS + 3];
+  if (k < CN_N - 1) {
+    const uint64_t v = cn[k];
+    if (v) atomicAdd((unsigned long long*)to, (unsigned long long)v);
+  } else {
+    if (abs_i0 != abs_e0) atomicAdd((unsigned long long*)net, (unsigned long long)(abs_i0 - abs_e0));
+  }
+  if (k < 2) {
+    const int64_t d = (int64_t)cn[CN_BIRTH + k] - (k ? abs_i0 + abs_i1 : abs_e0 + abs_e1);
+    if (d) atomicAdd((unsigned long long*)&B->n_live[k], (unsigned long long)d);
+  }
+}
+
 // Add a super-particle at x (cells) to the global charge of species s for the
 // next step (a birth), and to the cell histogram of the next sort.
 template <typename R>
@@ -686,16 +713,51 @@ __device__ __forceinline__ void deposit_global(int64_t* Qs, uint32_t* cell_count
 // U1-U2 (and U3-U4 for ionisation) the electron directions or U1-U4 the ion's
 // Maxwellian partner, U7 the waiting time to its next candidate.  An entry
 // marked redraw is an examination at a cut wait: it takes only the fresh wait.
+// The electron and the ion of an ionisation at x = xn: the electron's velocity
+// (ex, ey, ez) in m/s, the ion's Maxwellian at the gas temperature.
 template <typename R>
-__device__ __forceinline__ void mcc_candidate(const KArgs<R>& A, int s, int64_t k, bool redraw, uint32_t buf,
-                                              int64_t l, R xn, R un, R uy, R uz, uint64_t id, int64_t* Qn,
-                                              uint32_t* cell_count, uint32_t* cnt) {
+__device__ __forceinline__ void mcc_births(const KArgs<R>& A, uint32_t buf, int64_t l, R xn, R ex, R ey, R ez, uint64_t id,
+                                        int64_t* Qn, uint32_t* cell_count, uint32_t* cnt, unsigned long long* alloc,
+                                        int64_t base_e, int64_t base_i) {
   const CaseConst& c = A.c;
   Ctrl* C = A.ctrl;
+  // the slots first: their round trips to memory pass under the draws
+  const unsigned long long slots[2] = {atomicAdd(&alloc[0], 1ull) + (unsigned long long)base_e,
+                                       atomicAdd(&alloc[1], 1ull) + (unsigned long long)base_i};
   const int nodes = c.N + 1;
+  const R ivs = (R)c.inv_v_scale;
+  const Uniforms8<R> Ui = draw8<R>(id, (uint64_t)l, rng_tag(0, PU_ION), c.seed, c.case_id);
+  R g0, g1, g2n, g3;
+  box_muller<R>(Ui[0], Ui[1], g0, g1);
+  box_muller<R>(Ui[2], Ui[3], g2n, g3);
+  const R sg = (R)c.sig_gas;
+  const Words4 ch = philox4x64_10(id, (uint64_t)l, rng_tag(0, PU_CHILD), 0, c.seed, c.case_id);
+  const uint64_t cid[2] = {ch.w0, ch.w1};
+  const R cvx[2] = {ex, sg * g0}, cvy[2] = {ey, sg * g1}, cvz[2] = {ez, sg * g2n};
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const unsigned long long slot = slots[t];
+    if ((int64_t)slot >= c.capacity[t]) { atomicOr(&C->status, ST_CAPACITY); continue; }
+    const Uniforms8<double> Us = draw8<double>(cid[t], (uint64_t)l, rng_tag(t, PU_SKIP), c.seed, c.case_id);
+    A.p.xt[t][buf][slot] = xn;
+    A.p.ux[t][buf][slot] = cvx[t] * ivs;
+    A.p.cold[t][buf][slot] = Cold<R>{cvy[t] * ivs, cvz[t] * ivs, cid[t]};
+    A.p.next[t][buf][slot] = next_candidate(Us[0], l, c.log1m_p[t]);
+    deposit_global<R>(Qn + t * nodes, cell_count ? cell_count + t * c.N : nullptr, xn);
+    atomicAdd(&cnt[CN_BIRTH + t], 1u);
+  }
+}
+
+// U: its draw (collision_draw).  A birth takes slots base_e + alloc[0]++ and
+// base_i + alloc[1]++.
+template <typename R>
+__device__ __forceinline__ void mcc_candidate(const KArgs<R>& A, int s, int64_t k, bool redraw, uint32_t buf,
+                                              int64_t l, R xn, R un, R uy, R uz, uint64_t id, const Uniforms8<R>& U,
+                                              int64_t* Qn, uint32_t* cell_count, uint32_t* cnt,
+                                              unsigned long long* alloc, int64_t base_e = 0, int64_t base_i = 0) {
+  const CaseConst& c = A.c;
   const R vs = (R)c.v_scale, ivs = (R)c.inv_v_scale;
   R vx = un * vs, vy = uy * vs, vz = uz * vs;
-  const Uniforms8<R> U = draw8<R>(id, (uint64_t)l, rng_tag(s, PU_COLL), c.seed, c.case_id);
   if (redraw) {                            // a cut wait: only a fresh wait, from U7
     A.p.next[s][buf][k] = next_candidate((double)U[7], l, c.log1m_p[s]);
     return;
@@ -733,26 +795,7 @@ __device__ __forceinline__ void mcc_candidate(const KArgs<R>& A, int s, int64_t 
       vx = sp * nx; vy = sp * ny; vz = sp * nz;
       R mx, my, mz;
       iso_dir<R>(U[3], U[4], mx, my, mz);
-      const Uniforms8<R> Ui = draw8<R>(id, (uint64_t)l, rng_tag(0, PU_ION), c.seed, c.case_id);
-      R g0, g1, g2n, g3;
-      box_muller<R>(Ui[0], Ui[1], g0, g1);
-      box_muller<R>(Ui[2], Ui[3], g2n, g3);
-      const R sg = (R)c.sig_gas;
-      const Words4 ch = philox4x64_10(id, (uint64_t)l, rng_tag(0, PU_CHILD), 0, c.seed, c.case_id);
-      const uint64_t cid[2] = {ch.w0, ch.w1};
-      const R cvx[2] = {sp * mx, sg * g0}, cvy[2] = {sp * my, sg * g1}, cvz[2] = {sp * mz, sg * g2n};
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const unsigned long long slot = atomicAdd((unsigned long long*)&C->n_alloc[t], 1ull);
-        if ((int64_t)slot >= c.capacity[t]) { atomicOr(&C->status, ST_CAPACITY); continue; }
-        const Uniforms8<double> Us = draw8<double>(cid[t], (uint64_t)l, rng_tag(t, PU_SKIP), c.seed, c.case_id);
-        A.p.xt[t][buf][slot] = xn;
-        A.p.ux[t][buf][slot] = cvx[t] * ivs;
-        A.p.cold[t][buf][slot] = Cold<R>{cvy[t] * ivs, cvz[t] * ivs, cid[t]};
-        A.p.next[t][buf][slot] = next_candidate(Us[0], l, c.log1m_p[t]);
-        deposit_global<R>(Qn + t * nodes, cell_count ? cell_count + t * c.N : nullptr, xn);
-        atomicAdd(&cnt[CN_BIRTH + t], 1u);
-      }
+      mcc_births<R>(A, buf, l, xn, sp * mx, sp * my, sp * mz, id, Qn, cell_count, cnt, alloc, base_e, base_i);
     }
   } else {
     // Ar+: Maxwellian partner; resonant charge exchange hands over its velocity
@@ -778,6 +821,11 @@ __device__ __forceinline__ void mcc_candidate(const KArgs<R>& A, int s, int64_t 
     cr.uy = vy * ivs;
     cr.uz = vz * ivs;
   }
+}
+
+template <typename R>
+__device__ __forceinline__ Uniforms8<R> collision_draw(const CaseConst& c, int s, int64_t l, uint64_t id) {
+  return draw8<R>(id, (uint64_t)l, rng_tag(s, PU_COLL), c.seed, c.case_id);
 }
 
 // Sum of a 32-bit value over the 64 lanes of a wavefront, returned as a scalar:
@@ -829,7 +877,8 @@ __device__ __forceinline__ void wave_deposit(unsigned long long* sDep, int key, 
 // the global charge Qs of step l+1 -- one pair of 64-bit atomics per touched
 // cell -- and the counts to the cell histogram of the next sort; clear it.
 __device__ __forceinline__ void flush_tile(unsigned long long* sDep, int64_t* Qs, int N, uint32_t* cell_count) {
-  for (int i = threadIdx.x; i < N; i += kBlock) {
+  const int width = blockDim.x;
+  for (int i = threadIdx.x; i < N; i += width) {
     const uint64_t v = sDep[i];
     if (v) {
       const uint64_t cnt = v >> 48, sw = v & ((1ull << 48) - 1);
@@ -843,7 +892,8 @@ __device__ __forceinline__ void flush_tile(unsigned long long* sDep, int64_t* Qs
 
 // Add the LDS flux tile (int64 sums per node) to the 128-bit sums F and clear it.
 __device__ __forceinline__ void flush_flux(long long* sFlux, uint64_t* F, int nodes) {
-  for (int i = threadIdx.x; i < nodes; i += kBlock) {
+  const int width = blockDim.x;
+  for (int i = threadIdx.x; i < nodes; i += width) {
     const long long v = sFlux[i];
     if (v != 0) {
       atomic_add128(&F[2 * i], (int64_t)v);
@@ -1200,8 +1250,8 @@ __device__ __forceinline__ void mcc_block(const KArgs<R>& A, int bid, int nblk, 
 #pragma unroll
       for (int j = 0; j < kMccBatch; ++j)
         if (k[j] >= 0)
-          mcc_candidate<R>(A, s, k[j], redraw[j], buf, l, xu[j].x, xu[j].u, cr[j].uy, cr[j].uz, cr[j].id, Qn, cc,
-                           sh.cnt);
+          mcc_candidate<R>(A, s, k[j], redraw[j], buf, l, xu[j].x, xu[j].u, cr[j].uy, cr[j].uz, cr[j].id,
+                           collision_draw<R>(c, s, l, cr[j].id), Qn, cc, sh.cnt, (unsigned long long*)C->n_alloc);
     }
   }
   __syncthreads();
@@ -1290,6 +1340,615 @@ __device__ __forceinline__ void step_epilogue(const KArgs<R>& A, int64_t l, int 
     }
     C->done = 0;
   }
+}
+
+// ------------------------------------------------------------------ the fused step
+// k_fused is a whole time step in one launch: every workgroup reads the charge of
+// step l and solves the field for itself, pushes its particles, runs its own
+// collisions, and adds its charge to the entry of step l + 1.  The two-launch
+// step of a case that does not fill the device spends its time on a chain of
+// dependent round trips to memory -- field, candidate list, its counter, the
+// records, the done counter, the field solve of the last workgroup and its
+// publication -- and on the launch boundary in the middle of it.  Here the
+// candidates and the field stay in the workgroup, the records and random numbers
+// of its collisions are fetched and drawn while the field is solved, and no
+// workgroup waits for another.
+//
+// Nothing that a workgroup reads in a launch is written in it: the charge, the
+// births of a step (their slots lie behind the range of the step) and the net
+// charge absorbed at electrode 0 go into one of three entries.  The control
+// block keeps the state the launches started from (C->step, n_range, n_abs_net);
+// the launch's number i since then gives the step l = C->step + i and, modulo 3,
+// its entries, and the slot ranges move on through them.  k_commit writes the
+// state back after the last launch.
+//
+// What bounds it: latency.  Of a step of the paper's discharge (200k + 200k, 512
+// cells, FP32; 188 workgroups) 2.7 us pass until the inputs are there, 1.0 with
+// the candidate list, 2.8 in the field solve (the records' round trip and the
+// random numbers under it), 1.1 in the push, 0.6 to 4.5 in the collisions (the
+// births' chain of draws ends the step), 2 until the counters are written, and
+// 1.2 between launches.  Measured, us a step of an RF period, two launches ->
+// fused: 64 cells, 5k + 5k, FP64 21.5 -> 12.3; 777 cells, 60k + 60k, FP64 28.3 ->
+// 18.5; the paper's 24.8 -> 16.7; 1024 cells, 1M + 1M, FP32 31.3 -> 24.5, with
+// flux profiles and phase bins 39.0 -> 34.1.
+//
+// 512 threads with 4 slots a lane: the pass's loads are 16 bytes a lane, and two
+// workgroups fit on a CU within 128 VGPRs in FP32 (one of 512 in FP64).
+template <typename R>
+constexpr int kFusedThreads = 512;
+template <typename R>
+constexpr int kFusedTile = 4 * kFusedThreads<R>;       // slots of one pass
+
+// LDS: the field pairs, the charge tile of one species, the candidate list of a
+// pass, then the solve's arrays and, after it, the candidates' new positions and
+// velocities and the list of absorbed ions.
+template <typename R>
+__host__ __device__ constexpr size_t fused_list_bytes() {
+  return (size_t)kFusedTile<R> * (sizeof(XU<R>) + 4);
+}
+template <typename R>
+__host__ __device__ size_t fused_lds_bytes(int N, bool flux) {
+  const size_t solve = (size_t)(N + 1) * 16;
+  return (size_t)N * (sizeof(Pair<R>) + 8) + (flux ? (size_t)(N + 1) * 8 : 0) + (size_t)kFusedTile<R> * 4 +
+         (solve > fused_list_bytes<R>() ? solve : fused_list_bytes<R>()) + 16;
+}
+
+struct FusedShared {
+  uint32_t cnt[CN_N];
+  uint32_t qn, wn;
+  int64_t wq[4];
+  double wd[4];
+  double phi0;
+};
+
+template <typename R>
+struct FusedLds {
+  Pair<R>* Ep;                 // [N]
+  unsigned long long* dep;     // [N]
+  long long* flux;             // [N + 1]
+  uint32_t* cand;              // [kFusedTile] slot and redraw bit
+  int64_t* q;                  // [N + 1] net charge, until the field is solved
+  double* E;                   // [N + 1]
+  XU<R>* cxu;                  // [kFusedTile] from then on: x^(l+1) (-1: absorbed) and v_x of the candidates
+  uint32_t* wall;              // [kFusedTile] and the absorbed ions: slot, electrode in the top bit
+};
+
+// The slot range and the net absorbed charge at the start of step l = C->step + i.
+__device__ __forceinline__ void fused_state(const CaseConst& c, const Ctrl* C, int i, int i3, int64_t* range_e,
+                                            int64_t* range_i, int64_t* net) {
+  const int before = i3 == 0 ? 2 : i3 - 1;
+  *range_e = i ? min(C->range[before][0] + (int64_t)C->born[before][0], c.capacity[0]) : C->n_range[0];
+  *range_i = i ? min(C->range[before][1] + (int64_t)C->born[before][1], c.capacity[1]) : C->n_range[1];
+  *net = i ? C->net_sum[before] + C->net[before] : C->n_abs_net;
+}
+
+// Sums over a wavefront by DPP in the order of wave_incl_scan's last lane:
+// neighbours, then pairs of them, and so on (the additions commute, so every
+// lane of a pair may hold the sum).
+
+template <int kCtrl>
+__device__ __forceinline__ double dpp_move(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, kCtrl, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), kCtrl, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double lane_double(double v, int lane) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double wave_tree_sum(double v) {
+  v += dpp_move<0xB1>(v);      // quad_perm [1,0,3,2]
+  v += dpp_move<0x4E>(v);      // quad_perm [2,3,0,1]
+  v += dpp_move<0x141>(v);     // row_half_mirror: the other four of eight
+  v += dpp_move<0x140>(v);     // row_mirror: the other eight of sixteen
+  return (lane_double(v, 48) + lane_double(v, 32)) + (lane_double(v, 16) + lane_double(v, 0));
+}
+
+// Inclusive scan of 64-bit integers over a wavefront by DPP.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ int64_t dpp_add64(int64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, kCtrl, kRows, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)((uint64_t)v >> 32), kCtrl, kRows, 0xf, false);
+  return v + (int64_t)((uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ int64_t wave_scan64(int64_t v) {
+  v = dpp_add64<0x111, 0xf>(v);   // row_shr:1, 2, 4, 8
+  v = dpp_add64<0x112, 0xf>(v);
+  v = dpp_add64<0x114, 0xf>(v);
+  v = dpp_add64<0x118, 0xf>(v);
+  v = dpp_add64<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+  v = dpp_add64<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// The field solve of solve_field() for a fused step, and the field pairs.  The
+// first four wavefronts sum: the same partition of the nodes over 256 threads
+// and the same order of the floating-point sums, so the same bits; q becomes the
+// prefix sums S_m (S_0 = 0; q_0 and q_N keep apart).  Then every thread of the
+// workgroup evaluates nodes.  (With shuffles through LDS and four nodes a thread
+// this stage took 1.6 us of a step.)
+template <typename R, typename Idle>
+__device__ __forceinline__ void fused_solve(const CaseConst& c, int64_t* q, double V, double* sE, Pair<R>* Ep,
+                                            int64_t* s_wq, double* s_wd, double circ_num, double circ_den,
+                                            double* V0_out, Idle&& idle) {
+  constexpr int T = kFusedThreads<R>;
+  const int N = c.N, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int per = (N - 1 + kBlock - 1) / kBlock;
+  const int b = 1 + tid * per, e = min(b + per, N);
+  int64_t qv[kMaxPer] = {}, loc = 0, incl = 0;
+  if (tid < kBlock) {
+#pragma unroll
+    for (int t = 0; t < kMaxPer; ++t) {
+      qv[t] = (t < per && b + t < e) ? q[b + t] : 0;
+      loc += qv[t];
+    }
+    incl = wave_scan64(loc);
+    if (lane == 63) s_wq[w] = incl;
+  }
+  const int64_t q0 = q[0], qN = q[N];
+  __syncthreads();
+  if (tid < kBlock) {
+    int64_t S = incl - loc;
+#pragma unroll
+    for (int k = 0; k < kBlock / 64; ++k)
+      if (k < w) S += s_wq[k];
+    double tl = 0.0;
+#pragma unroll
+    for (int t = 0; t < kMaxPer; ++t) {
+      S += qv[t];
+      if (t < per && b + t < e) {
+        tl += (double)S;
+        q[b + t] = S;
+      }
+    }
+    const double x = wave_tree_sum(tl);
+    if (lane == 0) s_wd[w] = x;
+    if (tid == 0) q[0] = 0;
+  } else {
+    idle();
+  }
+  __syncthreads();
+  double Ts = 0.0;
+#pragma unroll
+  for (int k = 0; k < kBlock / 64; ++k) Ts += s_wd[k];
+  const double cp = c.c_phi, dx = c.dx;
+  if (circ_den > 0.0) V = (circ_num + c.e_w * 2.3283064365386963e-10 * (Ts / (double)N + (double)q0)) / circ_den;
+  if (tid == 0) *V0_out = V;
+  const double D0 = fma(cp, Ts, -V) / (double)N;
+  for (int m = tid; m <= N; m += T) {
+    const double D = m == N ? -fma(-cp, (double)q[N - 1], D0) : fma(-cp, (double)q[m], D0);
+    const double E = m == 0   ? -fma(cp, (double)q0, D0) / dx
+                     : m == N ? fma(cp, (double)qN, D) / dx
+                              : -(D + fma(-cp, (double)q[m - 1], D0)) / (2.0 * dx);
+    sE[m] = E;
+  }
+  __syncthreads();
+  publish_field<R>(c, sE, Ep, nullptr);
+}
+
+// The case's arguments, read anew: the loop over passes would otherwise keep
+// every constant of the collisions in a vector register throughout.
+template <typename R>
+__device__ __forceinline__ const KArgs<R>& fresh_case(const KArgs<R>& A) {
+  uintptr_t at = (uintptr_t)&A;
+  asm volatile("" : "+s"(at));
+  return case_of<R>(at, 0);
+}
+
+// Brings every line of a table in the constant address space into the scalar
+// cache at once (loaded where they are needed first, its lines cost a round
+// trip to memory each).  The loads complete in the block that issues them.
+template <size_t kBytes>
+__device__ __forceinline__ void warm_scalar_cache(uintptr_t at) {
+  static_assert(kBytes > 640 && kBytes <= 768, "lines of the table");
+  uint32_t a, b, c, d;
+  asm volatile(
+      "s_load_dword %0, %4, 0x0\n\ts_load_dword %1, %4, 0x40\n\ts_load_dword %2, %4, 0x80\n\t"
+      "s_load_dword %3, %4, 0xc0\n\ts_load_dword %0, %4, 0x100\n\ts_load_dword %1, %4, 0x140\n\t"
+      "s_load_dword %2, %4, 0x180\n\ts_load_dword %3, %4, 0x1c0\n\ts_load_dword %0, %4, 0x200\n\t"
+      "s_load_dword %1, %4, 0x240\n\ts_load_dword %2, %4, 0x280\n\ts_waitcnt lgkmcnt(0)"
+      : "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(d)
+      : "s"(at));
+}
+
+// One lane's four particles of a pass.
+template <typename R>
+struct Four {
+  R x[4], u[4];
+  uint32_t nx[4];
+};
+
+// Push of a wavefront's 256 particles, s uniform.  The arithmetic is that of
+// advance(), written out so that it rounds alike wherever it is compiled, and
+// without branches: what leaves the gap, and candidates, are looked at
+// afterwards by the lanes that have them.  due: the lane's particles that are
+// candidates (one bit each); their places in the list are at, at + 1, ...
+template <typename R, bool kFlux>
+__device__ __forceinline__ void fused_push(const KArgs<R>& A, const FusedLds<R>& L, FusedShared& sh, int s, int64_t k0,
+                                           int N, R factor, int dep_mode, uint32_t due, uint32_t at, Four<R>& f,
+                                           uint32_t& live) {
+#pragma clang fp contract(off)
+  R xn[4];
+  bool in[4], gone = false;
+  const R Nr = (R)N;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const R x = f.x[q];
+    const bool alive = !(x < (R)0);           // a NaN counts as alive until its new position shows it
+    const int j = max((int)x, 0);
+    if (kFlux && alive && x < Nr) {
+      long long a0, a1;
+      flux_shares<R>(x, j, f.u[q], a0, a1);
+      atomicAdd((unsigned long long*)&L.flux[j], (unsigned long long)a0);
+      atomicAdd((unsigned long long*)&L.flux[j + 1], (unsigned long long)a1);
+    }
+    const Pair<R> e = L.Ep[j];
+    // the electron velocity change, cells per step (factor 1 for electrons)
+    const R acc = dfma(x - (R)j, e.b, e.a) * factor;
+    f.u[q] = f.u[q] + acc;                    // v^(l+1/2) = v^(l-1/2) + (q/m) E dt
+    xn[q] = x + f.u[q];                       // x^(l+1) = x^(l) + v^(l+1/2) dt
+    in[q] = alive && xn[q] >= (R)0 && xn[q] < Nr;
+    gone |= alive && !in[q];
+    live += alive;
+  }
+  if (__ballot(gone)) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (f.x[q] < (R)0 || in[q]) continue;
+      if (xn[q] != xn[q]) {
+        atomicOr(&A.ctrl->status, ST_NUMERIC);
+        live -= f.x[q] != f.x[q];
+      } else {
+        const int el = xn[q] < (R)0 ? 0 : 1;
+        atomicAdd(&sh.cnt[CN_ABS + 2 * s + el], 1u);
+        if (s) L.wall[atomicAdd(&sh.wn, 1u)] = (uint32_t)(k0 + q) | (uint32_t)el << 31;
+      }
+    }
+  }
+  // the charge: all four particles of all lanes in one cell (sorted ions) are
+  // summed by DPP and added once, otherwise each particle adds to its cell
+  uint32_t W[4];
+  int key[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int jn = (int)xn[q];
+    key[q] = in[q] ? jn : -1;
+    W[q] = in[q] ? (uint32_t)frac_fixed(xn[q] - (R)jn) : 0u;
+    f.x[q] = in[q] ? xn[q] : (R)-1;
+  }
+  bool one = dep_mode != 0;
+  if (one) {
+    const int m = max(max(key[0], key[1]), max(key[2], key[3]));
+    const uint64_t any = __ballot(m >= 0);
+    const int k = any ? __builtin_amdgcn_readlane(m, (int)__builtin_ctzll(any)) : -1;
+    bool same = true;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) same = same && (key[q] < 0 || key[q] == k);
+    one = __all(same);
+    if (one && any) {
+      uint32_t lo = 0, hi = 0, n = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        lo += W[q] & 0xFFFFu;
+        hi += W[q] >> 16;
+        n += (uint32_t)__popcll(__ballot(in[q]));
+      }
+      const uint32_t a = dpp_wave_sum(lo), b = dpp_wave_sum(hi);
+      if (__lane_id() == 0)
+        atomicAdd(&L.dep[k], ((unsigned long long)n << 48) + ((unsigned long long)b << 16) + (unsigned long long)a);
+    }
+  }
+  if (!one) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (in[q]) atomicAdd(&L.dep[key[q]], (1ull << 48) + (unsigned long long)W[q]);
+  }
+  if (due) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (due >> q & 1u) L.cxu[at++] = XU<R>{f.x[q], f.u[q]};
+  }
+}
+
+// The absorbed ions of the list, then an empty list (uniform; complete at the call).
+template <typename R>
+__device__ __forceinline__ void fused_walls(const KArgs<R>& A0, const FusedLds<R>& L, FusedShared& sh, uint32_t buf) {
+  const uint32_t n = sh.wn;
+  if (n == 0) return;
+  const KArgs<R>& A = fresh_case<R>(A0);
+  for (uint32_t i = threadIdx.x; i < n; i += kFusedThreads<R>) {
+    const uint32_t e = L.wall[i];
+    const int64_t k = (int64_t)(e & 0x7FFFFFFFu);
+    const Cold<R> cr = A.p.cold[1][buf][k];
+    tally_ion<R>(A, (int)(e >> 31), A.p.ux[1][buf][k], cr.uy, cr.uz);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) sh.wn = 0;
+}
+
+// Workgroup b of G of step l = C->step + i of a case.
+template <typename R, bool kFlux>
+__device__ __forceinline__ void fused_block(const KArgs<R>& A, int b, int G, int i, int i3, int count_cells,
+                                            unsigned char* smem, FusedShared& sh) {
+  constexpr int T = kFusedThreads<R>, kTile = kFusedTile<R>;
+  const CaseConst& c = A.c;
+  const int N = c.N, nodes = N + 1, tid = threadIdx.x, lane = tid & 63;
+  FusedLds<R> L;
+  L.Ep = reinterpret_cast<Pair<R>*>(smem);
+  L.dep = reinterpret_cast<unsigned long long*>(L.Ep + N);
+  L.flux = reinterpret_cast<long long*>(L.dep + N);
+  L.cand = reinterpret_cast<uint32_t*>(L.flux + (kFlux ? nodes : 0));
+  unsigned char* rest =                      // kept an offset from smem: a pointer to LDS
+      smem + ((N * (sizeof(Pair<R>) + 8) + (kFlux ? nodes * 8 : 0) + kTile * 4 + 15) & ~(size_t)15);
+  L.q = reinterpret_cast<int64_t*>(rest);
+  L.E = reinterpret_cast<double*>(L.q + nodes);
+  L.cxu = reinterpret_cast<XU<R>*>(rest);
+  L.wall = reinterpret_cast<uint32_t*>(L.cxu + kTile);
+  Ctrl* C = A.ctrl;
+  const int64_t l = C->step + i;
+  const uint32_t buf = C->buf;
+  // what does not depend on the step before was left by it; the first launch
+  // after a commit works it out
+  const FusedNext next = i ? C->next[i & 1] : fused_next(c, l);
+  const int l3 = next.l3, l3n = l3 == 2 ? 0 : l3 + 1, l3c = 3 - l3 - l3n;   // this step, the next, the one before
+  const int pb = next.pb;
+  const int64_t* Q = A.g.Q + (int64_t)l3 * 2 * nodes;
+  int64_t* Qn = A.g.Q + (int64_t)l3n * 2 * nodes;
+  int64_t* Qc = A.g.Q + (int64_t)l3c * 2 * nodes;
+  int64_t range_e, range_i, n_net;
+  fused_state(c, C, i, i3, &range_e, &range_i, &n_net);
+  // tiles of both species in one numbering, electrons first; this workgroup
+  // takes every G-th, so that the workgroups stream neighbouring tiles
+  const int te = (int)((range_e + kTile - 1) / kTile), tiles = te + (int)((range_i + kTile - 1) / kTile);
+
+  // a pass's particles: each lane takes 4 consecutive slots
+  Four<R> f;
+  auto load = [&](int t) {
+    const int s = t >= te;
+    const R PM_GLOBAL* xs = A.p.xt[s][buf];
+    const R PM_GLOBAL* us = A.p.ux[s][buf];
+    const uint16_t PM_GLOBAL* ns = A.p.next[s][buf];
+    const int64_t end = s ? range_i : range_e;
+    const int64_t k0 = (int64_t)(s ? t - te : t) * kTile + 4 * tid;
+    if (k0 + 3 < end) {
+      const Vec4<R> xv = *(const Vec4<R> PM_GLOBAL*)(xs + k0);
+      const Vec4<R> uv = *(const Vec4<R> PM_GLOBAL*)(us + k0);
+      const Vec4<uint16_t> nv = *(const Vec4<uint16_t> PM_GLOBAL*)(ns + k0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        f.x[j] = xv[j];
+        f.u[j] = uv[j];
+        f.nx[j] = nv[j];
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bool in = k0 + j < end;
+        f.x[j] = in ? xs[k0 + j] : (R)-1;
+        f.u[j] = in ? us[k0 + j] : (R)0;
+        f.nx[j] = in ? ns[k0 + j] : 0u;
+      }
+    }
+  };
+  const bool solves = b < tiles || b == 0;
+  if (b < tiles) load(b);
+  // the charge entry of step l + 2 (last read by step l - 1) is cleared, and the
+  // charge of step l added to the averages, each node by one workgroup
+  for (int m = b + G * tid; m < 2 * nodes; m += G * T) {
+    const int64_t v = Q[m];
+    Qc[m] = 0;
+    add128(&A.g.sumQ[2 * m], v);
+    if (pb >= 0) add128(&A.g.sumQp[(int64_t)pb * 4 * nodes + 2 * m], v);
+  }
+  if (b == 0 && tid == T - 1) {
+    const int j3 = i3 == 2 ? 0 : i3 + 1;
+    C->range[i3][0] = range_e;
+    C->range[i3][1] = range_i;
+    C->born[j3][0] = C->born[j3][1] = 0;
+    C->net_sum[i3] = n_net;
+    C->net[j3] = 0;
+    C->next[(i + 1) & 1] = fused_next(c, l + 1);
+  }
+  if (solves) {
+    const bool self = !(c.flags & 1u);
+    for (int m = tid; m < nodes; m += T) L.q[m] = self ? Q[nodes + m] - Q[m] : 0;
+  }
+  if (tid < CN_N) sh.cnt[tid] = 0;
+  if (tid == 0) sh.qn = sh.wn = 0;
+  if (solves) {
+    for (int m = tid; m < N; m += T) L.dep[m] = 0ull;
+    if (kFlux)
+      for (int m = tid; m < nodes; m += T) L.flux[m] = 0;
+  }
+  __syncthreads();
+
+  const R ion = (R)c.ion_over_e;
+  const int dep_mode = c.dep_mode;
+  const uint32_t l15 = (uint32_t)l & 0x7FFFu;
+  unsigned long long* born = (unsigned long long*)C->born[i3];
+  uint32_t live = 0;
+  int used = 0;                              // passes in the charge (and flux) tile
+  bool fresh = true;                         // the field is still to be solved
+  int t = b;
+  while (true) {
+    const bool mine = t < tiles;
+    const int s = t >= te;
+    const int64_t k0 = (int64_t)(s ? t - te : t) * kTile + 4 * tid;
+    // the pass's candidates: the living that are due for examination (most of
+    // them are still there after the push)
+    uint32_t due = 0, at = 0;
+    if (mine && (s ? c.log1m_p[1] : c.log1m_p[0]) != 0.0) {
+      uint32_t before = 0, total = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool d = f.x[q] >= (R)0 && (f.nx[q] & 0x7FFFu) == l15;
+        due |= d ? 1u << q : 0u;
+        const uint64_t m = __ballot(d);
+        before += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        total += (uint32_t)__popcll(m);
+      }
+      if (total) {
+        if (lane == 0) at = atomicAdd(&sh.qn, total);
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + before;
+        uint32_t p = at;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (due >> q & 1u) L.cand[p++] = (uint32_t)(k0 + q) | ((f.nx[q] & kRedraw) << 16);
+      }
+    }
+    __syncthreads();
+    // one candidate a lane, the wavefronts that do not solve the field first:
+    // its record is fetched and its numbers are drawn meanwhile; whatever is
+    // left waits until the push is done
+    const int nc = (int)sh.qn;
+    const int ci = (tid + T / 2) & (T - 1);
+    uint32_t entry = 0;
+    Cold<R> cr = {};
+    Words4 words = {};
+    auto record = [&](int at) {
+      entry = L.cand[at];
+      cr = A.p.cold[s][buf][entry & 0x7FFFFFFFu];
+    };
+    auto draw = [&]() {
+      const KArgs<R>& B = fresh_case<R>(A);
+      words = philox4x64_10(cr.id, (uint64_t)l, rng_tag(s, PU_COLL), 0, B.c.seed, B.c.case_id);
+    };
+    auto fetch = [&](int at) {
+      record(at);
+      draw();
+    };
+    if (ci < nc) record(ci);
+    if (fresh) {
+      if (solves) {
+        double num = 0.0, den = 0.0;
+        if (c.cb > 0.0) {
+          num = C->sigma_init + c.cb * next.vs + c.e_w * (double)n_net;
+          den = c.cgap + c.cb;
+        }
+        fused_solve<R>(c, L.q, next.vs, L.E, L.Ep, sh.wq, sh.wd, num, den, &sh.phi0, [&]() {
+          if (ci < nc) draw();
+        });
+        __syncthreads();
+      }
+      if (ci < nc && tid < kBlock) draw();
+      fresh = false;
+    } else if (ci < nc) {
+      draw();
+    }
+    if (!mine) break;
+
+    fused_push<R, kFlux>(A, L, sh, s, k0, N, s ? ion : (R)1, dep_mode, due, at, f, live);
+    {
+      R PM_GLOBAL* xs = A.p.xt[s][buf];
+      R PM_GLOBAL* us = A.p.ux[s][buf];
+      const int64_t end = s ? range_i : range_e;
+      if (k0 + 3 < end) {
+        Vec4<R> xv, uv;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          xv[j] = f.x[j];
+          uv[j] = f.u[j];
+        }
+        *(Vec4<R> PM_GLOBAL*)(xs + k0) = xv;
+        *(Vec4<R> PM_GLOBAL*)(us + k0) = uv;
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (k0 + j < end) {
+            xs[k0 + j] = f.x[j];
+            us[k0 + j] = f.u[j];
+          }
+      }
+    }
+    ++used;
+    const bool more = t + G < tiles;
+    __syncthreads();
+    if (s) fused_walls<R>(A, L, sh, buf);
+    uint32_t tested = 0;
+    for (int r = 0; r < nc;) {               // rounds of one candidate a lane
+      const int at = r + ci;
+      const XU<R> xu = at < nc ? L.cxu[at] : XU<R>{(R)-1, (R)0};
+      if (!(xu.x < (R)0)) {                  // not absorbed
+        const bool redraw = (entry >> 31) != 0u;
+        tested += !redraw;
+        mcc_candidate<R>(fresh_case<R>(A), s, (int64_t)(entry & 0x7FFFFFFFu), redraw, buf, l, xu.x, xu.u, cr.uy, cr.uz,
+                         cr.id, Uniforms8<R>(words), Qn, count_cells ? A.g.cell_count : nullptr, sh.cnt, born, range_e, range_i);
+      }
+      r += T;
+      if (r + ci < nc) fetch(r + ci);
+    }
+    if (tested) atomicAdd(&sh.cnt[CN_CAND + s], tested);
+    // a cell of the charge tile counts 16 bits of slots, the flux tile
+    // kFluxFlushSlots; and the tiles are of one species
+    if (!more || (t + G >= te) != (bool)s || used == (kFlux ? (int)kFluxFlushSlots : kMaxSlotsPerBlock) / kTile) {
+      flush_tile(L.dep, Qn + s * nodes, N, count_cells ? A.g.cell_count + s * N : nullptr);
+      if (kFlux) flush_flux(L.flux, A.g.sumF + ((int64_t)(pb >= 0 ? pb : 0) * 2 + s) * 2 * nodes, nodes);
+      used = 0;
+    }
+    if (!more) break;
+    t += G;
+    load(t);
+    __syncthreads();
+    if (tid == 0) sh.qn = 0;
+    __syncthreads();
+  }
+
+  if (b == 0 && tid == T - 1) {
+    C->v_sum += sh.phi0;                     // the driven electrode's potential at t_l
+    C->avg_steps += 1;
+    if (pb >= 0) {
+      A.g.phase_v[pb] += sh.phi0;
+      A.g.phase_n[pb] += 1;
+    }
+    if (kFlux) A.g.flux_n[pb >= 0 ? pb : 0] += 1;
+  }
+  if (b >= tiles) return;
+  const uint32_t wl = dpp_wave_sum(live);
+  if (lane == 0) atomicAdd(&sh.cnt[CN_LIVE], wl);
+  __syncthreads();
+  fused_counters(C, bank_of(A.g, b), sh.cnt, &C->net[i3]);
+}
+
+template <typename R, bool kFlux>
+__global__ __launch_bounds__(kFusedThreads<R>) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 4 : 2)))
+void k_fused(KArgs<R> args, int i, int i3, int count_cells) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ FusedShared sh;
+  // the arguments lie in the constant address space themselves: read there like
+  // a batch's table (no second hop to it)
+  const KArgs<R>& A = case_of<R>((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr(), 0);
+  warm_scalar_cache<sizeof(KArgs<R>)>((uintptr_t)&A);
+  fused_block<R, kFlux>(A, blockIdx.x, gridDim.x, i, i3, count_cells, smem, sh);
+}
+
+// After n fused steps: the control block and the field of step C->step + n as
+// the two-launch steps leave them; the cells' sort offsets when a sort follows.
+template <typename R>
+__global__ __launch_bounds__(kBlock) void k_commit(uintptr_t args, int n, int count_cells) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const KArgs<R>& A = case_of<R>(args, 0);
+  Ctrl* C = A.ctrl;
+  const int64_t l = C->step + n;
+  int64_t range_e, range_i, net;
+  fused_state(A.c, C, n, n % 3, &range_e, &range_i, &net);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int j = 0; j < 3; ++j) {
+      C->born[j][0] = C->born[j][1] = 0;
+      C->net[j] = 0;
+    }
+    C->n_range[0] = C->n_alloc[0] = range_e;
+    C->n_range[1] = C->n_alloc[1] = range_i;
+    C->n_abs_net = net;
+    C->step = l;
+  }
+  __syncthreads();
+  FieldLds F = carve_field(smem, A.c.N);
+  field_for_step<R>(A, l, false, nullptr, F);
+  if (count_cells) scan_cells(A.c, A.g, C, F.wq);
 }
 
 // ------------------------------------------------------------------ diagnostics
@@ -1530,6 +2189,42 @@ hipError_t launch_diag_reset(const CaseConst& c, const GridPtrs& g, Ctrl* C, hip
   return hipGetLastError();
 }
 
+// Tiles of a case's particles in a fused step.
+template <typename R>
+int fused_tiles(int64_t n_e, int64_t n_i) {
+  const int64_t t = (n_e + kFusedTile<R> - 1) / kFusedTile<R> + (n_i + kFusedTile<R> - 1) / kFusedTile<R>;
+  return (int)(t > 1 ? t : 1);
+}
+
+// Workgroups of a fused step that fit on one CU at once.
+template <typename R>
+int fused_blocks_per_cu(int N, bool flux) {
+  int nb = 0;
+  const size_t lds = fused_lds_bytes<R>(N, flux);
+  const hipError_t e =
+      flux ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fused<R, true>, kFusedThreads<R>, lds)
+           : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fused<R, false>, kFusedThreads<R>, lds);
+  if (e != hipSuccess) return 1;
+  return nb > 0 ? nb : 1;
+}
+
+template <typename R>
+hipError_t launch_fused(const KArgs<R>& A, int grid, int i, int count_cells, hipStream_t st) {
+  const size_t lds = fused_lds_bytes<R>(A.c.N, A.c.flux != 0);
+  if (A.c.flux)
+    hipLaunchKernelGGL((k_fused<R, true>), dim3(grid), dim3(kFusedThreads<R>), lds, st, A, i, i % 3, count_cells);
+  else
+    hipLaunchKernelGGL((k_fused<R, false>), dim3(grid), dim3(kFusedThreads<R>), lds, st, A, i, i % 3, count_cells);
+  return hipGetLastError();
+}
+
+template <typename R>
+hipError_t launch_commit(const KArgs<R>& A, const KArgs<R>* dev_args, int n, int count_cells, hipStream_t st) {
+  hipLaunchKernelGGL(k_commit<R>, dim3(1), dim3(kBlock), field_lds_bytes(A.c.N), st, (uintptr_t)dev_args, n,
+                     count_cells);
+  return hipGetLastError();
+}
+
 #define PM_INSTANTIATE(R)                                                                                    \
   template hipError_t launch_load<R>(const KArgs<R>&, int64_t, int64_t, double, double, hipStream_t);      \
   template hipError_t launch_deposit_all<R>(const KArgs<R>&, int64_t, hipStream_t);                         \
@@ -1545,7 +2240,11 @@ hipError_t launch_diag_reset(const CaseConst& c, const GridPtrs& g, Ctrl* C, hip
   template hipError_t launch_step_batch<R>(const KArgs<R>*, const uint32_t*, const uint32_t*, int, int, int,  \
                                            int, int, hipStream_t);                                            \
   template hipError_t launch_sort_batch<R>(const KArgs<R>*, const uint32_t*, const uint32_t*, int, int,      \
-                                           hipStream_t);
+                                           hipStream_t);                                                       \
+  template int fused_blocks_per_cu<R>(int, bool);                                                              \
+  template int fused_tiles<R>(int64_t, int64_t);                                                               \
+  template hipError_t launch_fused<R>(const KArgs<R>&, int, int, int, hipStream_t);                            \
+  template hipError_t launch_commit<R>(const KArgs<R>&, const KArgs<R>*, int, int, hipStream_t);
 PM_INSTANTIATE(float)
 PM_INSTANTIATE(double)
 

@@ -32,6 +32,13 @@ constexpr uint32_t kIdleWork = 0xFFFFFFFFu;
 // sticky failure bits in Ctrl::status
 enum : uint32_t { ST_CAPACITY = 1u, ST_NUMERIC = 2u };
 
+// What a fused step needs to know of its step number, left by the step before.
+struct FusedNext {
+  double vs;                 // source voltage
+  int l3;                    // step mod 3
+  int pb;                    // phase bin (-1: none)
+};
+
 // Device-resident control block of one case.  Written by the last collision
 // workgroup of each step (the step epilogue) and read by every workgroup of the
 // next step.
@@ -60,7 +67,16 @@ struct Ctrl {
   uint32_t circ_ready;       // sigma_init recorded
   uint32_t pad32;
   uint64_t pad[3];
+  // Fused steps only (k_fused; all zero between a commit and the next of them,
+  // but range and net_sum): of launch i, at index i mod 3, its births, the net
+  // charge absorbed at electrode 0, and its slot ranges and the net charge before it.
+  uint64_t born[3][2];
+  int64_t net[3];
+  int64_t range[3][2];
+  int64_t net_sum[3];
+  FusedNext next[2];         // for launch i of them, at index i mod 2
 };
+static_assert(sizeof(Ctrl) <= 512, "the control block's place in the arena");
 
 // Step counters that every push and collision workgroup adds to, spread over
 // kBanks copies kBankStride bytes apart (workgroup b adds to copy b mod kBanks):
