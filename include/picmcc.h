@@ -425,8 +425,8 @@ pm_status pm_get_step_profile(pm_case* c, uint64_t* out, int64_t cap, int32_t* g
  * speed only: every shape computes the same particles (by id), charges and
  * diagnostics, because the random numbers depend on (seed, case_id, particle
  * id, step) and the charge sums are integers.  unroll, waves and work_groups
- * shape the push launch of a batch or of a single step of a case; several steps
- * of a case in one call choose their own grid. */
+ * shape the push launch of a single step; several steps in one call choose their
+ * own grid. */
 typedef struct {
   int32_t unroll;         /* particles per lane in flight: 8 or 16                      */
   int32_t waves;          /* register budget of the push kernel: 0 the compiler's own,  */
@@ -545,8 +545,8 @@ pm_status pm_batch_set_slot(pm_batch* b, int32_t slot, pm_case* c, void* hip_str
 
 /* --- measurement --------------------------------------------------------------
  * Advance n_steps steps with plain launches (the sorting schedule of pm_step),
- * each as a push and a collision launch, which is how a batch and a single step
- * of a case run (several steps of a case take one launch each), bracketing every push and collision launch with HIP events on the stream it
+ * each as a push and a collision launch, which is how a single step runs
+ * (several steps in one call take one launch each), bracketing every push and collision launch with HIP events on the stream it
  * runs on, and return the average duration of each kind of launch in ms.  A
  * batch runs its lanes one after another here, so each launch has the device
  * to itself.  Synchronises. */

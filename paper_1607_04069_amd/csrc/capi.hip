@@ -185,6 +185,20 @@ int resident_step_blocks(bool fp64, int N, int unroll, int waves, bool batch) {
   return per_cu * cus;
 }
 
+// Workgroups of a fused step resident on the whole device at once.
+int resident_fused_blocks(bool fp64, int N, bool flux, bool batch) {
+  int dev = 0, cus = 0;
+  (void)hipGetDevice(&dev);
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 1;
+  const int per_cu = fp64 ? pm::fused_blocks_per_cu<double>(N, flux, batch) : pm::fused_blocks_per_cu<float>(N, flux, batch);
+  return per_cu * cus;
+}
+
+// Passes of a fused step over the initial particles.
+int fused_tiles_of(const pm_case_params* p) {
+  return p->fp64 ? pm::fused_tiles<double>(p->np_e, p->np_i) : pm::fused_tiles<float>(p->np_e, p->np_i);
+}
+
 bool valid_shape(const pm_launch_shape* s) {
   return s && (s->unroll == 8 || s->unroll == 16) && (s->waves == 0 || s->waves == 6) && s->work_groups >= 0 &&
          s->deposit_mode >= 0 && s->deposit_mode <= 1 && s->sort_interval >= 0 && s->lanes >= 0 && s->lanes <= 4;
@@ -207,6 +221,15 @@ double expected_candidates(const pm_case_params* p, const pm::CaseConst& c) {
   double e = 0.0;
   for (int s = 0; s < 2; ++s) e += (double)(s ? p->np_i : p->np_e) * -std::expm1(c.log1m_p[s]);
   return e;
+}
+
+// What a case's fused step costs its workgroups, in particles pushed: a collision
+// candidate counts as 12 (10M + 10M particles on 512 cells: 130 us a step with
+// 82k candidates, 25 us more with 490k; the 64-discharge sweep, whose discharges
+// list 1 to 17% of their electrons, with shares by this 104 us a step in one lane,
+// by particles alone 117, with 6 or 20 for a candidate 106 and 112).
+double fused_work_of(const pm_case_params* p, const pm::CaseConst& c) {
+  return (double)(p->np_e + p->np_i) + 12.0 * expected_candidates(p, c);
 }
 
 // Expected candidates per collision lane: one while they fit in a resident wave
@@ -406,13 +429,7 @@ int sort_grid_for(const pm_case_params* p) {
 // the 978 of one pass each.)  Per-workgroup timestamps are taken of the two
 // launches only.
 int fused_grid_for(const pm_case_params* p, const pm::CaseConst& c) {
-  int dev = 0, cus = 0;
-  (void)hipGetDevice(&dev);
-  if (c.prof || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  const int per_cu = p->fp64 ? pm::fused_blocks_per_cu<double>(p->n_cells, c.flux != 0)
-                             : pm::fused_blocks_per_cu<float>(p->n_cells, c.flux != 0);
-  const int tiles = p->fp64 ? pm::fused_tiles<double>(p->np_e, p->np_i) : pm::fused_tiles<float>(p->np_e, p->np_i);
-  return std::min(tiles, per_cu * cus);
+  return c.prof ? 0 : std::min(fused_tiles_of(p), resident_fused_blocks(p->fp64, p->n_cells, c.flux != 0, false));
 }
 
 // Fewer steps than this up to a sort or the end of the call go by the two
@@ -1259,7 +1276,7 @@ pm_status pm_run_test_particles_static(const pm_tp_params* tp, const pm_tp_sourc
 // kernel (bandwidth-bound) fills the GPU.  A lane's work lists are a segment of
 // the batch's lists.
 struct BatchLane {
-  int step_off, step_n, mcc_off, mcc_n, sort_off, sort_n, maxN;
+  int step_off, step_n, mcc_off, mcc_n, sort_off, sort_n, fused_off, fused_n, maxN;
   hipStream_t st;          // nullptr for a single lane (the caller's stream)
   hipEvent_t done;
 };
@@ -1275,7 +1292,8 @@ struct pm_batch {
   hipEvent_t fork;
   char* arena;
   void* args;
-  uint32_t *step_nblk, *mcc_nblk, *sort_nblk, *step_work, *mcc_work, *sort_work;
+  uint32_t *step_nblk, *mcc_nblk, *sort_nblk, *fused_nblk, *step_work, *mcc_work, *sort_work, *fused_work;
+  bool fused;              // several steps of a call take one launch each
   hipStream_t cap_stream;
   hipGraph_t graph;
   hipGraphExec_t exec;
@@ -1291,7 +1309,7 @@ struct pm_batch {
 namespace {
 
 struct BatchLayout {
-  size_t args, step_nb, mcc_nb, sort_nb, step_work, mcc_work, sort_work, total;
+  size_t args, step_nb, mcc_nb, sort_nb, fused_nb, step_work, mcc_work, sort_work, fused_work, total;
 };
 
 // Upper bound of the workgroups of one launch resident on a device: at most
@@ -1311,9 +1329,11 @@ void slots_layout(int32_t n, bool fp64, int list_cap, BatchLayout* L) {
   L->step_nb = A.take((size_t)n * 4);
   L->mcc_nb = A.take((size_t)n * 4);
   L->sort_nb = A.take((size_t)n * 4);
+  L->fused_nb = A.take((size_t)n * 4);
   L->step_work = A.take((size_t)list_cap * 4);
   L->mcc_work = A.take((size_t)list_cap * 4);
   L->sort_work = A.take((size_t)list_cap * 4);
+  L->fused_work = A.take(((size_t)list_cap + n + 4) * 4);
   L->total = A.off;
 }
 
@@ -1339,9 +1359,11 @@ pm_status batch_layout(pm_case* const* cases, int32_t n, BatchLayout* L) {
   L->step_nb = A.take((size_t)n * 4);
   L->mcc_nb = A.take((size_t)n * 4);
   L->sort_nb = A.take((size_t)n * 4);
+  L->fused_nb = A.take((size_t)n * 4);
   L->step_work = A.take((size_t)steps * 4);
   L->mcc_work = A.take((size_t)mccs * 4);
   L->sort_work = A.take((size_t)sorts * 4);
+  L->fused_work = A.take(((size_t)max_resident_blocks() + 2 * n + 4) * 4);
   L->total = A.off;
   return PM_OK;
 }
@@ -1411,7 +1433,22 @@ pm_status write_tables(pm_batch* b, hipStream_t st) {
   const int64_t lane_mcc = std::min<int64_t>(resident_mcc / nl, b->list_cap / nl);
   const int64_t lane_sort = std::min<int64_t>(resident_mcc / nl, b->list_cap / nl);
   std::vector<pm::KArgs<R>> args(n);
-  std::vector<uint32_t> nb(n, 0), nm(n, 0), ns(n, 0), sw, mw, rw;
+  // fused steps: one resident wave of workgroups, half as many more where lanes
+  // run side by side and one lane's workgroups can start as another's end (64
+  // discharges in 3 lanes 99.9 -> 86.7 us a step, 16 in 2 lanes 28.0 -> 27.5, 8 in
+  // 2 lanes 21.8 -> 16.8; in a single lane the second generation costs more than
+  // the balance gives: 98.3 -> 110.9)
+  const int64_t resident_fused = std::min<int64_t>(
+      (int64_t)resident_fused_blocks(b->fp64, b->maxN, false, true) * (nl > 1 ? 3 : 2) / 2, max_resident_blocks());
+  const int64_t lane_fused = std::max<int64_t>(resident_fused / nl, (n + nl - 1) / nl);
+  double fused_work = 0.0;
+  bool fused = true;
+  for (const pm_case* c : b->cases)
+    if (c) {
+      fused_work += fused_work_of(&c->prm, c->c);
+      fused = fused && !c->c.prof;           // timestamps are taken of the two launches
+    }
+  std::vector<uint32_t> nb(n, 0), nm(n, 0), ns(n, 0), nf(n, 0), sw, mw, rw, fw;
   int64_t work_total = 0;
   std::vector<BatchLane> lanes(nl);
   for (int g = 0; g < nl; ++g) {
@@ -1453,8 +1490,21 @@ pm_status write_tables(pm_batch* b, hipStream_t st) {
     std::vector<double> cw(m);
     for (int k = 0; k < m; ++k) cw[k] = (double)(b->cases[mem[k]]->prm.capacity_e + b->cases[mem[k]]->prm.capacity_i);
     const std::vector<int64_t> sg = b->slotted ? shares(cw, lane_sort, scap) : std::vector<int64_t>();
+    // fused steps: in proportion to the cases' work
+    std::vector<int64_t> ft(m);
+    double lane_work = 0.0;
+    for (int k = 0; k < m; ++k) {
+      const pm_case* c = b->cases[mem[k]];
+      ft[k] = std::min(fused_tiles_of(&c->prm), 1 << 15);
+      wt[k] = fused_work_of(&c->prm, c->c);
+      lane_work += wt[k];
+    }
+    const std::vector<int64_t> fg = b->slotted
+        ? shares(wt, lane_fused, ft)
+        : shares(wt, std::max<int64_t>(m, (int64_t)((double)resident_fused * lane_work / std::max(fused_work, 1.0))), ft);
     BatchLane& L = lanes[g];
     L.maxN = b->slotted ? b->maxN : 0;
+    L.fused_off = (int)fw.size();
     L.step_off = (int)sw.size();
     L.mcc_off = (int)mw.size();
     L.sort_off = (int)rw.size();
@@ -1468,6 +1518,7 @@ pm_status write_tables(pm_batch* b, hipStream_t st) {
       nm[i] = (uint32_t)mcc_grid_for(&c->prm, c->c, per_lane);
       if (b->slotted) nm[i] = (uint32_t)std::min<int64_t>(nm[i], lane_mcc);
       ns[i] = (uint32_t)(b->slotted ? sg[k] : c->sort_grid);
+      nf[i] = (uint32_t)fg[k];
       work_total += ww;
       args[i] = args_of<R>(const_cast<pm_case*>(c));
       args[i].c.dep_mode = b->shape.deposit_mode;
@@ -1478,20 +1529,20 @@ pm_status write_tables(pm_batch* b, hipStream_t st) {
     // hardware starts workgroups in grid order, so the short ones fill the end
     // of the launch); tiles counted from the initial particles, as each
     // workgroup's strided share of its case's electron and ion tiles
-    {
-      const int64_t tile = (int64_t)256 * b->shape.unroll;
+    auto list = [&](std::vector<uint32_t>& out, int64_t tile, const std::vector<int64_t>& share) {
       std::vector<std::pair<int64_t, uint32_t>> ws;
-      for (int i : mem) {
-        const pm_case* c = b->cases[i];
+      for (int k = 0; k < m; ++k) {
+        const pm_case* c = b->cases[mem[k]];
         const int64_t te = (c->prm.np_e + tile - 1) / tile, ti = (c->prm.np_i + tile - 1) / tile;
-        const int64_t nw = nb[i] >> 16;
-        for (int64_t q = 0; q < nw; ++q)
-          ws.emplace_back(strided_count(0, te, q, nw) + strided_count(te, te + ti, q, nw),
-                          ((uint32_t)i << 16) | (uint32_t)q);
+        for (int64_t q = 0; q < share[k]; ++q)
+          ws.emplace_back(strided_count(0, te, q, share[k]) + strided_count(te, te + ti, q, share[k]),
+                          ((uint32_t)mem[k] << 16) | (uint32_t)q);
       }
       std::stable_sort(ws.begin(), ws.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
-      for (const auto& e : ws) sw.push_back(e.second);
-    }
+      for (const auto& e : ws) out.push_back(e.second);
+    };
+    list(sw, (int64_t)256 * b->shape.unroll, w);
+    list(fw, pm::fused_tile<R>(), fg);
     // workgroups that only rotate the charge buffers when a case outgrows its working share
     for (int i : mem)
       for (uint32_t q = nb[i] >> 16; q < (nb[i] & 0xFFFFu); ++q) sw.push_back(((uint32_t)i << 16) | q);
@@ -1502,15 +1553,17 @@ pm_status write_tables(pm_batch* b, hipStream_t st) {
     if (b->slotted) {
       // fixed lengths: idle entries after the lane's own
       if ((int64_t)sw.size() - L.step_off > lane_step || (int64_t)mw.size() - L.mcc_off > lane_mcc ||
-          (int64_t)rw.size() - L.sort_off > lane_sort)
+          (int64_t)rw.size() - L.sort_off > lane_sort || (int64_t)fw.size() - L.fused_off > lane_fused)
         return PM_EINVAL;
       sw.resize((size_t)(L.step_off + lane_step), pm::kIdleWork);
       mw.resize((size_t)(L.mcc_off + lane_mcc), pm::kIdleWork);
       rw.resize((size_t)(L.sort_off + lane_sort), pm::kIdleWork);
+      fw.resize((size_t)(L.fused_off + lane_fused), pm::kIdleWork);
     }
     L.step_n = (int)sw.size() - L.step_off;
     L.mcc_n = (int)mw.size() - L.mcc_off;
     L.sort_n = (int)rw.size() - L.sort_off;
+    L.fused_n = (int)fw.size() - L.fused_off;
   }
   PM_TRY(hipStreamSynchronize(st));      // no launch of the old tables may still read them
   // lane streams and events (the single lane runs on the caller's stream)
@@ -1530,11 +1583,13 @@ pm_status write_tables(pm_batch* b, hipStream_t st) {
     if (b->lanes[g].done) (void)hipEventDestroy(b->lanes[g].done);
   }
   // a slotted batch keeps its graph while only its members change (same lanes and lengths)
-  bool same_shape = b->slotted && b->exec && b->lanes.size() == lanes.size();
+  bool same_shape = b->slotted && b->exec && b->lanes.size() == lanes.size() && b->fused == fused;
   for (size_t g = 0; same_shape && g < lanes.size(); ++g)
     same_shape = b->lanes[g].step_n == lanes[g].step_n && b->lanes[g].mcc_n == lanes[g].mcc_n &&
-                 b->lanes[g].sort_n == lanes[g].sort_n && b->lanes[g].maxN == lanes[g].maxN;
+                 b->lanes[g].sort_n == lanes[g].sort_n && b->lanes[g].fused_n == lanes[g].fused_n &&
+                 b->lanes[g].maxN == lanes[g].maxN;
   b->lanes = lanes;
+  b->fused = fused;
   if (nl > 1 && !b->fork) PM_TRY(hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
   for (int i = 0; i < n; ++i)
     if (b->cases[i])
@@ -1543,6 +1598,8 @@ pm_status write_tables(pm_batch* b, hipStream_t st) {
   PM_TRY(hipMemcpyAsync(b->step_nblk, nb.data(), nb.size() * 4, hipMemcpyHostToDevice, st));
   PM_TRY(hipMemcpyAsync(b->mcc_nblk, nm.data(), nm.size() * 4, hipMemcpyHostToDevice, st));
   PM_TRY(hipMemcpyAsync(b->sort_nblk, ns.data(), ns.size() * 4, hipMemcpyHostToDevice, st));
+  PM_TRY(hipMemcpyAsync(b->fused_nblk, nf.data(), nf.size() * 4, hipMemcpyHostToDevice, st));
+  if (!fw.empty()) PM_TRY(hipMemcpyAsync(b->fused_work, fw.data(), fw.size() * 4, hipMemcpyHostToDevice, st));
   if (!sw.empty()) PM_TRY(hipMemcpyAsync(b->step_work, sw.data(), sw.size() * 4, hipMemcpyHostToDevice, st));
   if (!mw.empty()) PM_TRY(hipMemcpyAsync(b->mcc_work, mw.data(), mw.size() * 4, hipMemcpyHostToDevice, st));
   if (!rw.empty()) PM_TRY(hipMemcpyAsync(b->sort_work, rw.data(), rw.size() * 4, hipMemcpyHostToDevice, st));
@@ -1586,6 +1643,19 @@ pm_status lane_steps(pm_batch* b, const BatchLane& L, int64_t n, const std::vect
                      KernelTimer* tm = nullptr) {
   const auto* T = reinterpret_cast<const pm::KArgs<R>*>(b->args);
   for (int64_t i = 0; i < n; ++i) {
+    // the steps up to the next sort, each in one launch
+    int64_t m = 0;
+    while (!tm && b->fused && i + m < n && (m == 0 || !sorts[(size_t)(i + m - 1)])) ++m;
+    if (m >= kFusedMin) {
+      const int sort = sorts[(size_t)(i + m - 1)];
+      const uint32_t* work = b->fused_work + L.fused_off;
+      for (int64_t j = 0; j < m; ++j)
+        PM_TRY(pm::launch_fused_batch<R>(T, work, b->fused_nblk, L.fused_n, L.maxN, (int)j, sort && j == m - 1, st));
+      PM_TRY(pm::launch_commit_batch<R>(T, work, L.fused_n, L.maxN, (int)m, sort, st));
+      if (sort) PM_TRY(pm::launch_sort_batch<R>(T, b->sort_work + L.sort_off, b->sort_nblk, L.sort_n, L.maxN, st));
+      i += m - 1;
+      continue;
+    }
     const int sort = sorts[(size_t)i];
     if (tm) PM_TRY(hipEventRecord(tm->ev[0], st));
     PM_TRY(pm::launch_step_batch<R>(T, b->step_work + L.step_off, b->step_nblk, L.step_n, L.maxN,
@@ -1690,6 +1760,8 @@ pm_status pm_batch_create(pm_case* const* cases, int32_t n_cases, void* arena, s
   b->step_work = reinterpret_cast<uint32_t*>(b->arena + L.step_work);
   b->mcc_work = reinterpret_cast<uint32_t*>(b->arena + L.mcc_work);
   b->sort_work = reinterpret_cast<uint32_t*>(b->arena + L.sort_work);
+  b->fused_nblk = reinterpret_cast<uint32_t*>(b->arena + L.fused_nb);
+  b->fused_work = reinterpret_cast<uint32_t*>(b->arena + L.fused_work);
   b->cap_stream = nullptr;
   b->graph = nullptr;
   b->exec = nullptr;
@@ -1746,6 +1818,8 @@ pm_status pm_batch_create_slots(int32_t n_slots, int32_t fp64, int32_t steps_per
   b->step_work = reinterpret_cast<uint32_t*>(b->arena + L.step_work);
   b->mcc_work = reinterpret_cast<uint32_t*>(b->arena + L.mcc_work);
   b->sort_work = reinterpret_cast<uint32_t*>(b->arena + L.sort_work);
+  b->fused_nblk = reinterpret_cast<uint32_t*>(b->arena + L.fused_nb);
+  b->fused_work = reinterpret_cast<uint32_t*>(b->arena + L.fused_work);
   b->cap_stream = nullptr;
   b->graph = nullptr;
   b->exec = nullptr;

@@ -1362,15 +1362,25 @@ __device__ __forceinline__ void step_epilogue(const KArgs<R>& A, int64_t l, int 
 // its entries, and the slot ranges move on through them.  k_commit writes the
 // state back after the last launch.
 //
-// What bounds it: latency.  Of a step of the paper's discharge (200k + 200k, 512
-// cells, FP32; 188 workgroups) 2.7 us pass until the inputs are there, 1.0 with
-// the candidate list, 2.8 in the field solve (the records' round trip and the
-// random numbers under it), 1.1 in the push, 0.6 to 4.5 in the collisions (the
-// births' chain of draws ends the step), 2 until the counters are written, and
-// 1.2 between launches.  Measured, us a step of an RF period, two launches ->
-// fused: 64 cells, 5k + 5k, FP64 21.5 -> 12.3; 777 cells, 60k + 60k, FP64 28.3 ->
-// 18.5; the paper's 24.8 -> 16.7; 1024 cells, 1M + 1M, FP32 31.3 -> 24.5, with
-// flux profiles and phase bins 39.0 -> 34.1.
+// What bounds it in a case that does not fill the device: latency.  Of a step of
+// the paper's discharge (200k + 200k, 512 cells, FP32; 188 workgroups, one pass
+// each) 1.9 us pass until the inputs are there, 0.9 with the candidate list, 2.4
+// in the field solve (the records' round trip and the random numbers under it),
+// 1.1 in the push and store, 1.1 to 4 in the collisions (the births' chain of draws
+// ends the step), 2 until the counters are written, and 1.2 between launches.
+// Measured, us a step of an RF period, two launches -> fused: 64 cells, 5k + 5k,
+// FP64 21.5 -> 11.0; 777 cells, 60k + 60k, FP64 28.3 -> 17.1; the paper's 24.8 ->
+// 15.0; 1024 cells, 1M + 1M, FP32 31.3 -> 23.1, with flux profiles and phase bins
+// 39.0 -> 32.5.
+//
+// In a large case or batch: a quarter each go to waiting for particles, to the
+// push, and to the collisions' arithmetic (10M + 10M, 512 cells, 3 Pa: 130 us a
+// step, 360 MB at 2.8 TB/s; two launches 160).  What helped there: candidates
+// listed over many passes and collided 512 at a time (in each pass a few lanes'
+// collisions kept the whole workgroup waiting: 139 -> 117 us a step of the
+// 64-discharge sweep), one barrier a pass, and the next pass's loads issued
+// before the collisions with nothing done to them there (117 -> 101).  A whole
+// pass ahead they cost more in registers than they gave (103).
 //
 // 512 threads with 4 slots a lane: the pass's loads are 16 bytes a lane, and two
 // workgroups fit on a CU within 128 VGPRs in FP32 (one of 512 in FP64).
@@ -1379,23 +1389,25 @@ constexpr int kFusedThreads = 512;
 template <typename R>
 constexpr int kFusedTile = 4 * kFusedThreads<R>;       // slots of one pass
 
-// LDS: the field pairs, the charge tile of one species, the candidate list of a
-// pass, then the solve's arrays and, after it, the candidates' new positions and
-// velocities and the list of absorbed ions.
+// LDS: the field pairs, the charge tile of one species, the candidate list, then
+// the solve's arrays and, after it, the candidates' new positions and velocities
+// and the list of absorbed ions.
+template <typename R>
+constexpr int kFusedList = kFusedTile<R> + 1024;       // candidates: at most a pass's more than are waited for
 template <typename R>
 __host__ __device__ constexpr size_t fused_list_bytes() {
-  return (size_t)kFusedTile<R> * (sizeof(XU<R>) + 4);
+  return (size_t)kFusedList<R> * sizeof(XU<R>) + (size_t)kFusedTile<R> * 4;
 }
 template <typename R>
 __host__ __device__ size_t fused_lds_bytes(int N, bool flux) {
   const size_t solve = (size_t)(N + 1) * 16;
-  return (size_t)N * (sizeof(Pair<R>) + 8) + (flux ? (size_t)(N + 1) * 8 : 0) + (size_t)kFusedTile<R> * 4 +
+  return (size_t)N * (sizeof(Pair<R>) + 8) + (flux ? (size_t)(N + 1) * 8 : 0) + (size_t)kFusedList<R> * 4 +
          (solve > fused_list_bytes<R>() ? solve : fused_list_bytes<R>()) + 16;
 }
 
 struct FusedShared {
   uint32_t cnt[CN_N];
-  uint32_t qn, wn;
+  uint32_t qn[3], wn;          // candidates of a pass, at its number mod 3; absorbed ions listed
   int64_t wq[4];
   double wd[4];
   double phi0;
@@ -1406,20 +1418,24 @@ struct FusedLds {
   Pair<R>* Ep;                 // [N]
   unsigned long long* dep;     // [N]
   long long* flux;             // [N + 1]
-  uint32_t* cand;              // [kFusedTile] slot and redraw bit
+  uint32_t* cand;              // [kFusedList] slot and redraw bit
   int64_t* q;                  // [N + 1] net charge, until the field is solved
   double* E;                   // [N + 1]
-  XU<R>* cxu;                  // [kFusedTile] from then on: x^(l+1) (-1: absorbed) and v_x of the candidates
+  XU<R>* cxu;                  // [kFusedList] from then on: x^(l+1) (-1: absorbed) and v_x of the candidates
   uint32_t* wall;              // [kFusedTile] and the absorbed ions: slot, electrode in the top bit
 };
 
 // The slot range and the net absorbed charge at the start of step l = C->step + i.
 __device__ __forceinline__ void fused_state(const CaseConst& c, const Ctrl* C, int i, int i3, int64_t* range_e,
                                             int64_t* range_i, int64_t* net) {
+  // all loaded before any is used
   const int before = i3 == 0 ? 2 : i3 - 1;
-  *range_e = i ? min(C->range[before][0] + (int64_t)C->born[before][0], c.capacity[0]) : C->n_range[0];
-  *range_i = i ? min(C->range[before][1] + (int64_t)C->born[before][1], c.capacity[1]) : C->n_range[1];
-  *net = i ? C->net_sum[before] + C->net[before] : C->n_abs_net;
+  const int64_t r0 = C->range[before][0], r1 = C->range[before][1], b0 = (int64_t)C->born[before][0],
+                b1 = (int64_t)C->born[before][1], ns = C->net_sum[before], nt = C->net[before];
+  const int64_t f0 = C->n_range[0], f1 = C->n_range[1], fn = C->n_abs_net;
+  *range_e = i ? min(r0 + b0, c.capacity[0]) : f0;
+  *range_i = i ? min(r1 + b1, c.capacity[1]) : f1;
+  *net = i ? ns + nt : fn;
 }
 
 // Sums over a wavefront by DPP in the order of wave_incl_scan's last lane:
@@ -1538,12 +1554,12 @@ __device__ __forceinline__ const KArgs<R>& fresh_case(const KArgs<R>& A) {
   return case_of<R>(at, 0);
 }
 
-// Brings every line of a table in the constant address space into the scalar
-// cache at once (loaded where they are needed first, its lines cost a round
-// trip to memory each).  The loads complete in the block that issues them.
-template <size_t kBytes>
-__device__ __forceinline__ void warm_scalar_cache(uintptr_t at) {
-  static_assert(kBytes > 640 && kBytes <= 768, "lines of the table");
+// Brings every line of the arguments and of the control block into the scalar
+// cache, in two round trips (loaded where they are needed first, each line costs
+// one).  The loads complete in the blocks that issue them.
+template <typename R>
+__device__ __forceinline__ void warm_scalar_cache(const KArgs<R>& A) {
+  static_assert(sizeof(KArgs<R>) > 640 && sizeof(KArgs<R>) <= 768 && sizeof(Ctrl) > 448, "lines loaded below");
   uint32_t a, b, c, d;
   asm volatile(
       "s_load_dword %0, %4, 0x0\n\ts_load_dword %1, %4, 0x40\n\ts_load_dword %2, %4, 0x80\n\t"
@@ -1551,14 +1567,21 @@ __device__ __forceinline__ void warm_scalar_cache(uintptr_t at) {
       "s_load_dword %2, %4, 0x180\n\ts_load_dword %3, %4, 0x1c0\n\ts_load_dword %0, %4, 0x200\n\t"
       "s_load_dword %1, %4, 0x240\n\ts_load_dword %2, %4, 0x280\n\ts_waitcnt lgkmcnt(0)"
       : "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(d)
-      : "s"(at));
+      : "s"((uintptr_t)&A));
+  asm volatile(
+      "s_load_dword %0, %4, 0x0\n\ts_load_dword %1, %4, 0x40\n\ts_load_dword %2, %4, 0x80\n\t"
+      "s_load_dword %3, %4, 0xc0\n\ts_load_dword %0, %4, 0x100\n\ts_load_dword %1, %4, 0x140\n\t"
+      "s_load_dword %2, %4, 0x180\n\ts_load_dword %3, %4, 0x1c0\n\ts_waitcnt lgkmcnt(0)"
+      : "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(d)
+      : "s"((uintptr_t)A.ctrl));
 }
 
-// One lane's four particles of a pass.
+// One lane's four particles of a pass, as loaded (taken apart or put into other
+// registers at the load, they would be waited for there).
 template <typename R>
 struct Four {
-  R x[4], u[4];
-  uint32_t nx[4];
+  Vec4<R> x, u;
+  Vec4<uint16_t> nx;
 };
 
 // Push of a wavefront's 256 particles, s uniform.  The arithmetic is that of
@@ -1682,67 +1705,47 @@ __device__ __forceinline__ void fused_block(const KArgs<R>& A, int b, int G, int
   L.flux = reinterpret_cast<long long*>(L.dep + N);
   L.cand = reinterpret_cast<uint32_t*>(L.flux + (kFlux ? nodes : 0));
   unsigned char* rest =                      // kept an offset from smem: a pointer to LDS
-      smem + ((N * (sizeof(Pair<R>) + 8) + (kFlux ? nodes * 8 : 0) + kTile * 4 + 15) & ~(size_t)15);
+      smem + ((N * (sizeof(Pair<R>) + 8) + (kFlux ? nodes * 8 : 0) + kFusedList<R> * 4 + 15) & ~(size_t)15);
   L.q = reinterpret_cast<int64_t*>(rest);
   L.E = reinterpret_cast<double*>(L.q + nodes);
   L.cxu = reinterpret_cast<XU<R>*>(rest);
-  L.wall = reinterpret_cast<uint32_t*>(L.cxu + kTile);
+  L.wall = reinterpret_cast<uint32_t*>(L.cxu + kFusedList<R>);
   Ctrl* C = A.ctrl;
-  const int64_t l = C->step + i;
-  const uint32_t buf = C->buf;
+  // the state that the launch reads, by scalar loads (nothing of it is written in
+  // it): one round trip to memory for all of it
+  using CP = const Ctrl __attribute__((address_space(4)))*;
+  const Ctrl* S = (const Ctrl*)(CP)(uintptr_t)C;
+  int64_t range_e, range_i, n_net;
+  fused_state(c, S, i, i3, &range_e, &range_i, &n_net);
+  const int64_t l = S->step + i;
+  const uint32_t buf = S->buf;
   // what does not depend on the step before was left by it; the first launch
   // after a commit works it out
-  const FusedNext next = i ? C->next[i & 1] : fused_next(c, l);
+  FusedNext next = S->next[i & 1];
+  if (i == 0) next = fused_next(c, l);
   const int l3 = next.l3, l3n = l3 == 2 ? 0 : l3 + 1, l3c = 3 - l3 - l3n;   // this step, the next, the one before
   const int pb = next.pb;
   const int64_t* Q = A.g.Q + (int64_t)l3 * 2 * nodes;
   int64_t* Qn = A.g.Q + (int64_t)l3n * 2 * nodes;
   int64_t* Qc = A.g.Q + (int64_t)l3c * 2 * nodes;
-  int64_t range_e, range_i, n_net;
-  fused_state(c, C, i, i3, &range_e, &range_i, &n_net);
   // tiles of both species in one numbering, electrons first; this workgroup
   // takes every G-th, so that the workgroups stream neighbouring tiles
   const int te = (int)((range_e + kTile - 1) / kTile), tiles = te + (int)((range_i + kTile - 1) / kTile);
 
-  // a pass's particles: each lane takes 4 consecutive slots
+  // a pass's particles: each lane takes 4 consecutive slots.  A lane beyond the
+  // range loads its last slots instead (the arrays are whole multiples of 256
+  // bytes, so the four slots at a multiple of 4 are always inside).
   Four<R> f;
   auto load = [&](int t) {
     const int s = t >= te;
-    const R PM_GLOBAL* xs = A.p.xt[s][buf];
-    const R PM_GLOBAL* us = A.p.ux[s][buf];
-    const uint16_t PM_GLOBAL* ns = A.p.next[s][buf];
     const int64_t end = s ? range_i : range_e;
-    const int64_t k0 = (int64_t)(s ? t - te : t) * kTile + 4 * tid;
-    if (k0 + 3 < end) {
-      const Vec4<R> xv = *(const Vec4<R> PM_GLOBAL*)(xs + k0);
-      const Vec4<R> uv = *(const Vec4<R> PM_GLOBAL*)(us + k0);
-      const Vec4<uint16_t> nv = *(const Vec4<uint16_t> PM_GLOBAL*)(ns + k0);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        f.x[j] = xv[j];
-        f.u[j] = uv[j];
-        f.nx[j] = nv[j];
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const bool in = k0 + j < end;
-        f.x[j] = in ? xs[k0 + j] : (R)-1;
-        f.u[j] = in ? us[k0 + j] : (R)0;
-        f.nx[j] = in ? ns[k0 + j] : 0u;
-      }
-    }
+    const int64_t k = min((int64_t)(s ? t - te : t) * kTile + 4 * tid, (end - 1) & ~(int64_t)3);
+    f.x = *(const Vec4<R> PM_GLOBAL*)(A.p.xt[s][buf] + k);
+    f.u = *(const Vec4<R> PM_GLOBAL*)(A.p.ux[s][buf] + k);
+    f.nx = *(const Vec4<uint16_t> PM_GLOBAL*)(A.p.next[s][buf] + k);
   };
   const bool solves = b < tiles || b == 0;
   if (b < tiles) load(b);
-  // the charge entry of step l + 2 (last read by step l - 1) is cleared, and the
-  // charge of step l added to the averages, each node by one workgroup
-  for (int m = b + G * tid; m < 2 * nodes; m += G * T) {
-    const int64_t v = Q[m];
-    Qc[m] = 0;
-    add128(&A.g.sumQ[2 * m], v);
-    if (pb >= 0) add128(&A.g.sumQp[(int64_t)pb * 4 * nodes + 2 * m], v);
-  }
   if (b == 0 && tid == T - 1) {
     const int j3 = i3 == 2 ? 0 : i3 + 1;
     C->range[i3][0] = range_e;
@@ -1756,8 +1759,17 @@ __device__ __forceinline__ void fused_block(const KArgs<R>& A, int b, int G, int
     const bool self = !(c.flags & 1u);
     for (int m = tid; m < nodes; m += T) L.q[m] = self ? Q[nodes + m] - Q[m] : 0;
   }
+  // the charge entry of step l + 2 (last read by step l - 1) is cleared, and the
+  // charge of step l added to the averages, each node by one workgroup
+  for (int m = b + G * tid; m < 2 * nodes; m += G * T) {
+    const int64_t v = Q[m];
+    Qc[m] = 0;
+    add128(&A.g.sumQ[2 * m], v);
+    if (pb >= 0) add128(&A.g.sumQp[(int64_t)pb * 4 * nodes + 2 * m], v);
+  }
   if (tid < CN_N) sh.cnt[tid] = 0;
-  if (tid == 0) sh.qn = sh.wn = 0;
+  if (tid < 3) sh.qn[tid] = 0;
+  if (tid == 0) sh.wn = 0;
   if (solves) {
     for (int m = tid; m < N; m += T) L.dep[m] = 0ull;
     if (kFlux)
@@ -1771,15 +1783,33 @@ __device__ __forceinline__ void fused_block(const KArgs<R>& A, int b, int G, int
   unsigned long long* born = (unsigned long long*)C->born[i3];
   uint32_t live = 0;
   int used = 0;                              // passes in the charge (and flux) tile
-  bool fresh = true;                         // the field is still to be solved
-  int t = b;
-  while (true) {
+  const bool only = b + G >= tiles;          // a single pass
+  int nc = 0, p3 = 0;                        // candidates listed; the pass's number mod 3
+  const int ci = (tid + T / 2) & (T - 1);    // the wavefronts that do not solve the field first
+  uint32_t entry = 0;
+  Cold<R> cr = {};
+  Words4 words = {};
+  auto record = [&](int s, int at) {
+    entry = L.cand[at];
+    cr = A.p.cold[s][buf][entry & 0x7FFFFFFFu];
+  };
+  auto draw = [&](int s) {
+    const KArgs<R>& B = fresh_case<R>(A);
+    words = philox4x64_10(cr.id, (uint64_t)l, rng_tag(s, PU_COLL), 0, B.c.seed, B.c.case_id);
+  };
+  for (int t = b;;) {
     const bool mine = t < tiles;
     const int s = t >= te;
     const int64_t k0 = (int64_t)(s ? t - te : t) * kTile + 4 * tid;
-    // the pass's candidates: the living that are due for examination (most of
-    // them are still there after the push)
-    uint32_t due = 0, at = 0;
+    const int64_t end = s ? range_i : range_e;
+    if (mine && k0 + 3 >= end) {             // no particles beyond the range
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (k0 + q >= end) f.x[q] = (R)-1;
+    }
+    // the pass's candidates join the list: the living that are due for
+    // examination (most of them are still there after the push)
+    uint32_t due = 0, at = (uint32_t)nc;
     if (mine && (s ? c.log1m_p[1] : c.log1m_p[0]) != 0.0) {
       uint32_t before = 0, total = 0;
 #pragma unroll
@@ -1791,52 +1821,36 @@ __device__ __forceinline__ void fused_block(const KArgs<R>& A, int b, int G, int
         total += (uint32_t)__popcll(m);
       }
       if (total) {
-        if (lane == 0) at = atomicAdd(&sh.qn, total);
-        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + before;
-        uint32_t p = at;
+        uint32_t first = 0;
+        if (lane == 0) first = atomicAdd(&sh.qn[p3], total);
+        at += (uint32_t)__builtin_amdgcn_readfirstlane((int)first) + before;
+        uint32_t e = at;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          if (due >> q & 1u) L.cand[p++] = (uint32_t)(k0 + q) | ((f.nx[q] & kRedraw) << 16);
+          if (due >> q & 1u) L.cand[e++] = (uint32_t)(k0 + q) | ((uint32_t)(f.nx[q] & kRedraw) << 16);
       }
     }
     __syncthreads();
-    // one candidate a lane, the wavefronts that do not solve the field first:
-    // its record is fetched and its numbers are drawn meanwhile; whatever is
-    // left waits until the push is done
-    const int nc = (int)sh.qn;
-    const int ci = (tid + T / 2) & (T - 1);
-    uint32_t entry = 0;
-    Cold<R> cr = {};
-    Words4 words = {};
-    auto record = [&](int at) {
-      entry = L.cand[at];
-      cr = A.p.cold[s][buf][entry & 0x7FFFFFFFu];
-    };
-    auto draw = [&]() {
-      const KArgs<R>& B = fresh_case<R>(A);
-      words = philox4x64_10(cr.id, (uint64_t)l, rng_tag(s, PU_COLL), 0, B.c.seed, B.c.case_id);
-    };
-    auto fetch = [&](int at) {
-      record(at);
-      draw();
-    };
-    if (ci < nc) record(ci);
-    if (fresh) {
+    nc += (int)sh.qn[p3];
+    p3 = p3 == 2 ? 0 : p3 + 1;               // the entry of the pass after the next is the one before this
+    if (tid == 0) sh.qn[p3 == 2 ? 0 : p3 + 1] = 0;
+    if (t == b) {
+      // a single pass's first candidate of each lane: its record is fetched and
+      // its numbers are drawn while the field is solved
+      const bool early = only && ci < nc;
+      if (early) record(s, ci);
       if (solves) {
         double num = 0.0, den = 0.0;
         if (c.cb > 0.0) {
-          num = C->sigma_init + c.cb * next.vs + c.e_w * (double)n_net;
+          num = S->sigma_init + c.cb * next.vs + c.e_w * (double)n_net;
           den = c.cgap + c.cb;
         }
         fused_solve<R>(c, L.q, next.vs, L.E, L.Ep, sh.wq, sh.wd, num, den, &sh.phi0, [&]() {
-          if (ci < nc) draw();
+          if (early) draw(s);
         });
         __syncthreads();
       }
-      if (ci < nc && tid < kBlock) draw();
-      fresh = false;
-    } else if (ci < nc) {
-      draw();
+      if (early && tid < kBlock) draw(s);
     }
     if (!mine) break;
 
@@ -1844,16 +1858,9 @@ __device__ __forceinline__ void fused_block(const KArgs<R>& A, int b, int G, int
     {
       R PM_GLOBAL* xs = A.p.xt[s][buf];
       R PM_GLOBAL* us = A.p.ux[s][buf];
-      const int64_t end = s ? range_i : range_e;
       if (k0 + 3 < end) {
-        Vec4<R> xv, uv;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          xv[j] = f.x[j];
-          uv[j] = f.u[j];
-        }
-        *(Vec4<R> PM_GLOBAL*)(xs + k0) = xv;
-        *(Vec4<R> PM_GLOBAL*)(us + k0) = uv;
+        *(Vec4<R> PM_GLOBAL*)(xs + k0) = f.x;
+        *(Vec4<R> PM_GLOBAL*)(us + k0) = f.u;
       } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -1865,35 +1872,41 @@ __device__ __forceinline__ void fused_block(const KArgs<R>& A, int b, int G, int
     }
     ++used;
     const bool more = t + G < tiles;
-    __syncthreads();
+    if (more) load(t + G);                   // the next pass's particles come in meanwhile
+    // a cell of the charge tile counts 16 bits of slots, the flux tile
+    // kFluxFlushSlots; and the tiles are of one species
+    const bool flush = !more || (t + G >= te) != (bool)s ||
+                       used == (kFlux ? (int)kFluxFlushSlots : kMaxSlotsPerBlock) / kTile;
+    const bool collide = flush || nc > kFusedList<R> - kTile;
+    if (s || collide) __syncthreads();
     if (s) fused_walls<R>(A, L, sh, buf);
-    uint32_t tested = 0;
-    for (int r = 0; r < nc;) {               // rounds of one candidate a lane
-      const int at = r + ci;
-      const XU<R> xu = at < nc ? L.cxu[at] : XU<R>{(R)-1, (R)0};
-      if (!(xu.x < (R)0)) {                  // not absorbed
+    if (collide) {
+      uint32_t tested = 0;
+      for (int r = 0; r < nc; r += T) {      // rounds of one candidate a lane
+        const int at = r + ci;
+        const XU<R> xu = at < nc ? L.cxu[at] : XU<R>{(R)-1, (R)0};
+        if (xu.x < (R)0) continue;           // absorbed
+        if (!only || r) {
+          record(s, at);
+          draw(s);
+        }
         const bool redraw = (entry >> 31) != 0u;
         tested += !redraw;
         mcc_candidate<R>(fresh_case<R>(A), s, (int64_t)(entry & 0x7FFFFFFFu), redraw, buf, l, xu.x, xu.u, cr.uy, cr.uz,
-                         cr.id, Uniforms8<R>(words), Qn, count_cells ? A.g.cell_count : nullptr, sh.cnt, born, range_e, range_i);
+                         cr.id, Uniforms8<R>(words), Qn, count_cells ? A.g.cell_count : nullptr, sh.cnt, born, range_e,
+                         range_i);
       }
-      r += T;
-      if (r + ci < nc) fetch(r + ci);
+      if (tested) atomicAdd(&sh.cnt[CN_CAND + s], tested);
+      nc = 0;
     }
-    if (tested) atomicAdd(&sh.cnt[CN_CAND + s], tested);
-    // a cell of the charge tile counts 16 bits of slots, the flux tile
-    // kFluxFlushSlots; and the tiles are of one species
-    if (!more || (t + G >= te) != (bool)s || used == (kFlux ? (int)kFluxFlushSlots : kMaxSlotsPerBlock) / kTile) {
+    if (flush) {
       flush_tile(L.dep, Qn + s * nodes, N, count_cells ? A.g.cell_count + s * N : nullptr);
       if (kFlux) flush_flux(L.flux, A.g.sumF + ((int64_t)(pb >= 0 ? pb : 0) * 2 + s) * 2 * nodes, nodes);
       used = 0;
     }
     if (!more) break;
     t += G;
-    load(t);
-    __syncthreads();
-    if (tid == 0) sh.qn = 0;
-    __syncthreads();
+    if (collide) __syncthreads();            // the list is read
   }
 
   if (b == 0 && tid == T - 1) {
@@ -1920,16 +1933,32 @@ void k_fused(KArgs<R> args, int i, int i3, int count_cells) {
   // the arguments lie in the constant address space themselves: read there like
   // a batch's table (no second hop to it)
   const KArgs<R>& A = case_of<R>((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr(), 0);
-  warm_scalar_cache<sizeof(KArgs<R>)>((uintptr_t)&A);
+  warm_scalar_cache<R>(A);
   fused_block<R, kFlux>(A, blockIdx.x, gridDim.x, i, i3, count_cells, smem, sh);
+}
+
+// A fused step of a batch (no flux profiles there): the workgroups of the work
+// list, as in k_step_batch.  Measured, us a step, two launches -> fused: 64
+// discharges of the sweep in 3 lanes 97.3 -> 86.7, in one 98.6 -> 98.3; 12 of them
+// in a slotted batch, 2 lanes, 32.3 -> 21; 3 in one lane 23.7 -> 13.0; 32 in FP64,
+// 3 lanes, 92.1 -> 79.7.
+template <typename R>
+__global__ __launch_bounds__(kFusedThreads<R>) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 4 : 2)))
+void k_fused_batch(uintptr_t cases, const uint32_t* __restrict__ work, const uint32_t* __restrict__ nblocks, int i,
+                   int i3, int count_cells) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ FusedShared sh;
+  const uint32_t w = work[blockIdx.x];
+  if (w == kIdleWork) return;
+  const KArgs<R>& A = case_of<R>(cases, w >> 16);
+  warm_scalar_cache<R>(A);
+  fused_block<R, false>(A, (int)(w & 0xFFFFu), (int)nblocks[w >> 16], i, i3, count_cells, smem, sh);
 }
 
 // After n fused steps: the control block and the field of step C->step + n as
 // the two-launch steps leave them; the cells' sort offsets when a sort follows.
 template <typename R>
-__global__ __launch_bounds__(kBlock) void k_commit(uintptr_t args, int n, int count_cells) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  const KArgs<R>& A = case_of<R>(args, 0);
+__device__ __forceinline__ void commit_block(const KArgs<R>& A, int n, int count_cells, unsigned char* smem) {
   Ctrl* C = A.ctrl;
   const int64_t l = C->step + n;
   int64_t range_e, range_i, net;
@@ -1949,6 +1978,22 @@ __global__ __launch_bounds__(kBlock) void k_commit(uintptr_t args, int n, int co
   FieldLds F = carve_field(smem, A.c.N);
   field_for_step<R>(A, l, false, nullptr, F);
   if (count_cells) scan_cells(A.c, A.g, C, F.wq);
+}
+
+template <typename R>
+__global__ __launch_bounds__(kBlock) void k_commit(uintptr_t args, int n, int count_cells) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  commit_block<R>(case_of<R>(args, 0), n, count_cells, smem);
+}
+
+// The commit of every case that has a workgroup 0 in the work list.
+template <typename R>
+__global__ __launch_bounds__(kBlock) void k_commit_batch(uintptr_t cases, const uint32_t* __restrict__ work, int n,
+                                                         int count_cells) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const uint32_t w = work[blockIdx.x];
+  if (w == kIdleWork || (w & 0xFFFFu) != 0) return;
+  commit_block<R>(case_of<R>(cases, w >> 16), n, count_cells, smem);
 }
 
 // ------------------------------------------------------------------ diagnostics
@@ -2189,6 +2234,9 @@ hipError_t launch_diag_reset(const CaseConst& c, const GridPtrs& g, Ctrl* C, hip
   return hipGetLastError();
 }
 
+template <typename R>
+int fused_tile() { return kFusedTile<R>; }
+
 // Tiles of a case's particles in a fused step.
 template <typename R>
 int fused_tiles(int64_t n_e, int64_t n_i) {
@@ -2196,14 +2244,15 @@ int fused_tiles(int64_t n_e, int64_t n_i) {
   return (int)(t > 1 ? t : 1);
 }
 
-// Workgroups of a fused step that fit on one CU at once.
+// Workgroups of a fused step (plain or batched) that fit on one CU at once.
 template <typename R>
-int fused_blocks_per_cu(int N, bool flux) {
+int fused_blocks_per_cu(int N, bool flux, bool batch) {
   int nb = 0;
   const size_t lds = fused_lds_bytes<R>(N, flux);
   const hipError_t e =
-      flux ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fused<R, true>, kFusedThreads<R>, lds)
-           : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fused<R, false>, kFusedThreads<R>, lds);
+      batch  ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fused_batch<R>, kFusedThreads<R>, lds)
+      : flux ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fused<R, true>, kFusedThreads<R>, lds)
+             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fused<R, false>, kFusedThreads<R>, lds);
   if (e != hipSuccess) return 1;
   return nb > 0 ? nb : 1;
 }
@@ -2225,6 +2274,22 @@ hipError_t launch_commit(const KArgs<R>& A, const KArgs<R>* dev_args, int n, int
   return hipGetLastError();
 }
 
+template <typename R>
+hipError_t launch_fused_batch(const KArgs<R>* cases, const uint32_t* work, const uint32_t* nblocks, int grid, int maxN,
+                              int i, int count_cells, hipStream_t st) {
+  hipLaunchKernelGGL(k_fused_batch<R>, dim3(grid), dim3(kFusedThreads<R>), fused_lds_bytes<R>(maxN, false), st,
+                     (uintptr_t)cases, work, nblocks, i, i % 3, count_cells);
+  return hipGetLastError();
+}
+
+template <typename R>
+hipError_t launch_commit_batch(const KArgs<R>* cases, const uint32_t* work, int grid, int maxN, int n, int count_cells,
+                               hipStream_t st) {
+  hipLaunchKernelGGL(k_commit_batch<R>, dim3(grid), dim3(kBlock), field_lds_bytes(maxN), st, (uintptr_t)cases, work, n,
+                     count_cells);
+  return hipGetLastError();
+}
+
 #define PM_INSTANTIATE(R)                                                                                    \
   template hipError_t launch_load<R>(const KArgs<R>&, int64_t, int64_t, double, double, hipStream_t);      \
   template hipError_t launch_deposit_all<R>(const KArgs<R>&, int64_t, hipStream_t);                         \
@@ -2241,7 +2306,11 @@ hipError_t launch_commit(const KArgs<R>& A, const KArgs<R>* dev_args, int n, int
                                            int, int, hipStream_t);                                            \
   template hipError_t launch_sort_batch<R>(const KArgs<R>*, const uint32_t*, const uint32_t*, int, int,      \
                                            hipStream_t);                                                       \
-  template int fused_blocks_per_cu<R>(int, bool);                                                              \
+  template int fused_blocks_per_cu<R>(int, bool, bool);                                                        \
+  template hipError_t launch_fused_batch<R>(const KArgs<R>*, const uint32_t*, const uint32_t*, int, int, int,  \
+                                            int, hipStream_t);                                                 \
+  template hipError_t launch_commit_batch<R>(const KArgs<R>*, const uint32_t*, int, int, int, int, hipStream_t); \
+  template int fused_tile<R>();                                                                                \
   template int fused_tiles<R>(int64_t, int64_t);                                                               \
   template hipError_t launch_fused<R>(const KArgs<R>&, int, int, int, hipStream_t);                            \
   template hipError_t launch_commit<R>(const KArgs<R>&, const KArgs<R>*, int, int, hipStream_t);

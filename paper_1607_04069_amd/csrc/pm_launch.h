@@ -31,11 +31,17 @@ template <typename R> hipError_t launch_step_batch(const KArgs<R>* cases, const 
 template <typename R> hipError_t launch_sort_batch(const KArgs<R>* cases, const uint32_t* work,
                                                    const uint32_t* nblocks, int grid, int maxN, hipStream_t);
 // fused steps: launch i since the last commit; the commit after n of them
-template <typename R> int fused_blocks_per_cu(int N, bool flux);
+template <typename R> int fused_blocks_per_cu(int N, bool flux, bool batch);
 template <typename R> int fused_tiles(int64_t n_e, int64_t n_i);
+template <typename R> int fused_tile();                        // slots of a pass
 template <typename R> hipError_t launch_fused(const KArgs<R>& A, int grid, int i, int count_cells, hipStream_t);
 template <typename R> hipError_t launch_commit(const KArgs<R>& A, const KArgs<R>* dev_args, int n, int count_cells,
                                                hipStream_t);
+template <typename R> hipError_t launch_fused_batch(const KArgs<R>* cases, const uint32_t* work,
+                                                    const uint32_t* nblocks, int grid, int maxN, int i,
+                                                    int count_cells, hipStream_t);
+template <typename R> hipError_t launch_commit_batch(const KArgs<R>* cases, const uint32_t* work, int grid, int maxN,
+                                                     int n, int count_cells, hipStream_t);
 hipError_t launch_scan_cells(const CaseConst&, const GridPtrs&, Ctrl*, hipStream_t);
 hipError_t launch_diag_reset(const CaseConst&, const GridPtrs&, Ctrl*, hipStream_t);
 
