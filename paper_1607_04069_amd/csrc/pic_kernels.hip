@@ -1367,20 +1367,23 @@ __device__ __forceinline__ void step_epilogue(const KArgs<R>& A, int64_t l, int 
 // each) 1.9 us pass until the inputs are there, 0.9 with the candidate list, 2.4
 // in the field solve (the records' round trip and the random numbers under it),
 // 1.1 in the push and store, 1.1 to 4 in the collisions (the births' chain of draws
-// ends the step), 2 until the counters are written, and 1.2 between launches.
-// Measured, us a step of an RF period, two launches -> fused: 64 cells, 5k + 5k,
-// FP64 21.5 -> 11.0; 777 cells, 60k + 60k, FP64 28.3 -> 17.1; the paper's 24.8 ->
-// 15.0; 1024 cells, 1M + 1M, FP32 31.3 -> 23.1, with flux profiles and phase bins
-// 39.0 -> 32.5.
+// ends the step), 2 until the counters are written, and the rest until the next
+// launch: outstanding atomics, caches, 1.2 of launch.  Measured, us a step of an
+// RF period, two launches -> fused: 64 cells, 5k + 5k, FP64 21.5 -> 10.9; 777 cells,
+// 60k + 60k, FP64 28.3 -> 17.2; the paper's 24.8 -> 14.9; 1024 cells, 1M + 1M, FP32
+// 31.3 -> 21.1, with flux profiles and phase bins 39.0 -> 31.5.
 //
-// In a large case or batch: a quarter each go to waiting for particles, to the
-// push, and to the collisions' arithmetic (10M + 10M, 512 cells, 3 Pa: 130 us a
-// step, 360 MB at 2.8 TB/s; two launches 160).  What helped there: candidates
-// listed over many passes and collided 512 at a time (in each pass a few lanes'
-// collisions kept the whole workgroup waiting: 139 -> 117 us a step of the
-// 64-discharge sweep), one barrier a pass, and the next pass's loads issued
-// before the collisions with nothing done to them there (117 -> 101).  A whole
-// pass ahead they cost more in registers than they gave (103).
+// In a large case or batch a quarter each goes to waiting for particles, to the
+// push, and to the collisions' arithmetic (10M + 10M, 512 cells, 3 Pa: 115 us a
+// step, 360 MB at 3.1 TB/s; two launches 160).  What helped there, in us a step of
+// it or of the 64-discharge sweep in 3 lanes: candidates listed over all of a
+// workgroup's passes and collided 512 at a time (in each pass a few lanes'
+// collisions kept the whole workgroup waiting: sweep 139 -> 117; with those of both
+// species in one list 130 -> 126); the next pass's loads issued before the collisions with
+// nothing done to them there (sweep 117 -> 101); one atomic a node in the flush of
+// the charge instead of two (126 -> 117).  A whole pass ahead the loads cost more
+// in registers than they gave (sweep 103), and runs of neighbouring tiles for a
+// workgroup, which touch fewer cells, gave nothing (118).
 //
 // 512 threads with 4 slots a lane: the pass's loads are 16 bytes a lane, and two
 // workgroups fit on a CU within 128 VGPRs in FP32 (one of 512 in FP64).
@@ -1393,10 +1396,10 @@ constexpr int kFusedTile = 4 * kFusedThreads<R>;       // slots of one pass
 // the solve's arrays and, after it, the candidates' new positions and velocities
 // and the list of absorbed ions.
 template <typename R>
-constexpr int kFusedList = kFusedTile<R> + 1024;       // candidates: at most a pass's more than are waited for
+constexpr int kFusedList = kFusedTile<R> + 1024;       // candidates: a pass may add a whole tile
 template <typename R>
 __host__ __device__ constexpr size_t fused_list_bytes() {
-  return (size_t)kFusedList<R> * sizeof(XU<R>) + (size_t)kFusedTile<R> * 4;
+  return (size_t)kFusedList<R> * sizeof(XU<R>) + (size_t)2 * kFusedTile<R> * 4;
 }
 template <typename R>
 __host__ __device__ size_t fused_lds_bytes(int N, bool flux) {
@@ -1407,7 +1410,7 @@ __host__ __device__ size_t fused_lds_bytes(int N, bool flux) {
 
 struct FusedShared {
   uint32_t cnt[CN_N];
-  uint32_t qn[3], wn;          // candidates of a pass, at its number mod 3; absorbed ions listed
+  uint32_t qn[3], wn[3];       // candidates and absorbed ions of a pass, at its number mod 3
   int64_t wq[4];
   double wd[4];
   double phi0;
@@ -1422,7 +1425,7 @@ struct FusedLds {
   int64_t* q;                  // [N + 1] net charge, until the field is solved
   double* E;                   // [N + 1]
   XU<R>* cxu;                  // [kFusedList] from then on: x^(l+1) (-1: absorbed) and v_x of the candidates
-  uint32_t* wall;              // [kFusedTile] and the absorbed ions: slot, electrode in the top bit
+  uint32_t* wall;              // [2][kFusedTile] and the absorbed ions of a pass, at its number mod 2: slot, electrode in the top bit
 };
 
 // The slot range and the net absorbed charge at the start of step l = C->step + i.
@@ -1584,6 +1587,35 @@ struct Four {
   Vec4<uint16_t> nx;
 };
 
+// A lane's four values of a pass to the tile's slots, in FP32 written through the
+// cache of the XCD: left dirty there, they are written back after the launch's last
+// workgroup, before the next launch starts (1M + 1M particles, 1024 cells: 22.1 ->
+// 21.2 us a step; 5k + 5k in FP64 10.9 either way, and no faster at 60k + 60k).
+template <typename R>
+__device__ __forceinline__ void store_tile(R PM_GLOBAL* tile, const Vec4<R>& v) {
+  if constexpr (sizeof(R) == 4) {
+    using U4 = uint32_t __attribute__((ext_vector_type(4)));
+    constexpr int kDeviceScope = 16;         // sc1
+    const __amdgpu_buffer_rsrc_t d =
+        __builtin_amdgcn_make_buffer_rsrc((void*)(R*)tile, 0, (int)(kFusedTile<R> * sizeof(R)), 0x00027000);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, v), d, (int)(threadIdx.x * 16), 0, kDeviceScope);
+  } else {
+    *(Vec4<R> PM_GLOBAL*)(tile + 4 * threadIdx.x) = v;
+  }
+}
+
+// The cell that all of a wavefront's keys name (-1: none; -2: more than one).
+__device__ __forceinline__ int one_cell(const int (&key)[4]) {
+  const int m = max(max(key[0], key[1]), max(key[2], key[3]));
+  const uint64_t any = __ballot(m >= 0);
+  if (!any) return -1;
+  const int k = __builtin_amdgcn_readlane(m, (int)__builtin_ctzll(any));
+  bool same = true;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) same = same && (key[q] < 0 || key[q] == k);
+  return __all(same) ? k : -2;
+}
+
 // Push of a wavefront's 256 particles, s uniform.  The arithmetic is that of
 // advance(), written out so that it rounds alike wherever it is compiled, and
 // without branches: what leaves the gap, and candidates, are looked at
@@ -1591,23 +1623,48 @@ struct Four {
 // candidates (one bit each); their places in the list are at, at + 1, ...
 template <typename R, bool kFlux>
 __device__ __forceinline__ void fused_push(const KArgs<R>& A, const FusedLds<R>& L, FusedShared& sh, int s, int64_t k0,
-                                           int N, R factor, int dep_mode, uint32_t due, uint32_t at, Four<R>& f,
-                                           uint32_t& live) {
+                                           int N, R factor, int dep_mode, uint32_t due, uint32_t at, uint32_t* wall,
+                                           uint32_t* wn, Four<R>& f, uint32_t& live) {
 #pragma clang fp contract(off)
   R xn[4];
   bool in[4], gone = false;
   const R Nr = (R)N;
+  if (kFlux) {
+    // a wavefront in one cell (sorted ions) adds its sums once, otherwise each
+    // particle adds its shares: 64 lanes at one address take turns (1M + 1M, 1024
+    // cells, phase bins: 32.3 -> 31.5 us a step)
+    int key[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) key[q] = !(f.x[q] < (R)0) && f.x[q] < Nr ? max((int)f.x[q], 0) : -1;
+    const int k = one_cell(key);
+    int64_t s0 = 0, s1 = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (key[q] < 0) continue;
+      long long a0, a1;
+      flux_shares<R>(f.x[q], key[q], f.u[q], a0, a1);
+      if (k >= 0) {
+        s0 += a0;
+        s1 += a1;
+      } else {
+        atomicAdd((unsigned long long*)&L.flux[key[q]], (unsigned long long)a0);
+        atomicAdd((unsigned long long*)&L.flux[key[q] + 1], (unsigned long long)a1);
+      }
+    }
+    if (k >= 0) {
+      s0 = wave_scan64(s0);
+      s1 = wave_scan64(s1);
+      if (__lane_id() == 63) {
+        atomicAdd((unsigned long long*)&L.flux[k], (unsigned long long)s0);
+        atomicAdd((unsigned long long*)&L.flux[k + 1], (unsigned long long)s1);
+      }
+    }
+  }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const R x = f.x[q];
     const bool alive = !(x < (R)0);           // a NaN counts as alive until its new position shows it
     const int j = max((int)x, 0);
-    if (kFlux && alive && x < Nr) {
-      long long a0, a1;
-      flux_shares<R>(x, j, f.u[q], a0, a1);
-      atomicAdd((unsigned long long*)&L.flux[j], (unsigned long long)a0);
-      atomicAdd((unsigned long long*)&L.flux[j + 1], (unsigned long long)a1);
-    }
     const Pair<R> e = L.Ep[j];
     // the electron velocity change, cells per step (factor 1 for electrons)
     const R acc = dfma(x - (R)j, e.b, e.a) * factor;
@@ -1627,7 +1684,7 @@ __device__ __forceinline__ void fused_push(const KArgs<R>& A, const FusedLds<R>&
       } else {
         const int el = xn[q] < (R)0 ? 0 : 1;
         atomicAdd(&sh.cnt[CN_ABS + 2 * s + el], 1u);
-        if (s) L.wall[atomicAdd(&sh.wn, 1u)] = (uint32_t)(k0 + q) | (uint32_t)el << 31;
+        if (s) wall[atomicAdd(wn, 1u)] = (uint32_t)(k0 + q) | (uint32_t)el << 31;
       }
     }
   }
@@ -1642,29 +1699,19 @@ __device__ __forceinline__ void fused_push(const KArgs<R>& A, const FusedLds<R>&
     W[q] = in[q] ? (uint32_t)frac_fixed(xn[q] - (R)jn) : 0u;
     f.x[q] = in[q] ? xn[q] : (R)-1;
   }
-  bool one = dep_mode != 0;
-  if (one) {
-    const int m = max(max(key[0], key[1]), max(key[2], key[3]));
-    const uint64_t any = __ballot(m >= 0);
-    const int k = any ? __builtin_amdgcn_readlane(m, (int)__builtin_ctzll(any)) : -1;
-    bool same = true;
+  const int k = dep_mode != 0 ? one_cell(key) : -2;
+  if (k >= 0) {
+    uint32_t lo = 0, hi = 0, n = 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) same = same && (key[q] < 0 || key[q] == k);
-    one = __all(same);
-    if (one && any) {
-      uint32_t lo = 0, hi = 0, n = 0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        lo += W[q] & 0xFFFFu;
-        hi += W[q] >> 16;
-        n += (uint32_t)__popcll(__ballot(in[q]));
-      }
-      const uint32_t a = dpp_wave_sum(lo), b = dpp_wave_sum(hi);
-      if (__lane_id() == 0)
-        atomicAdd(&L.dep[k], ((unsigned long long)n << 48) + ((unsigned long long)b << 16) + (unsigned long long)a);
+    for (int q = 0; q < 4; ++q) {
+      lo += W[q] & 0xFFFFu;
+      hi += W[q] >> 16;
+      n += (uint32_t)__popcll(__ballot(in[q]));
     }
-  }
-  if (!one) {
+    const uint32_t a = dpp_wave_sum(lo), b = dpp_wave_sum(hi);
+    if (__lane_id() == 0)
+      atomicAdd(&L.dep[k], ((unsigned long long)n << 48) + ((unsigned long long)b << 16) + (unsigned long long)a);
+  } else if (k == -2) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       if (in[q]) atomicAdd(&L.dep[key[q]], (1ull << 48) + (unsigned long long)W[q]);
@@ -1676,20 +1723,17 @@ __device__ __forceinline__ void fused_push(const KArgs<R>& A, const FusedLds<R>&
   }
 }
 
-// The absorbed ions of the list, then an empty list (uniform; complete at the call).
+// The n absorbed ions of the list.
 template <typename R>
-__device__ __forceinline__ void fused_walls(const KArgs<R>& A0, const FusedLds<R>& L, FusedShared& sh, uint32_t buf) {
-  const uint32_t n = sh.wn;
+__device__ __forceinline__ void fused_walls(const KArgs<R>& A0, const uint32_t* wall, int n, uint32_t buf) {
   if (n == 0) return;
   const KArgs<R>& A = fresh_case<R>(A0);
-  for (uint32_t i = threadIdx.x; i < n; i += kFusedThreads<R>) {
-    const uint32_t e = L.wall[i];
+  for (int i = threadIdx.x; i < n; i += kFusedThreads<R>) {
+    const uint32_t e = wall[i];
     const int64_t k = (int64_t)(e & 0x7FFFFFFFu);
     const Cold<R> cr = A.p.cold[1][buf][k];
     tally_ion<R>(A, (int)(e >> 31), A.p.ux[1][buf][k], cr.uy, cr.uz);
   }
-  __syncthreads();
-  if (threadIdx.x == 0) sh.wn = 0;
 }
 
 // Workgroup b of G of step l = C->step + i of a case.
@@ -1768,8 +1812,7 @@ __device__ __forceinline__ void fused_block(const KArgs<R>& A, int b, int G, int
     if (pb >= 0) add128(&A.g.sumQp[(int64_t)pb * 4 * nodes + 2 * m], v);
   }
   if (tid < CN_N) sh.cnt[tid] = 0;
-  if (tid < 3) sh.qn[tid] = 0;
-  if (tid == 0) sh.wn = 0;
+  if (tid < 3) sh.qn[tid] = sh.wn[tid] = 0;
   if (solves) {
     for (int m = tid; m < N; m += T) L.dep[m] = 0ull;
     if (kFlux)
@@ -1784,7 +1827,9 @@ __device__ __forceinline__ void fused_block(const KArgs<R>& A, int b, int G, int
   uint32_t live = 0;
   int used = 0;                              // passes in the charge (and flux) tile
   const bool only = b + G >= tiles;          // a single pass
-  int nc = 0, p3 = 0;                        // candidates listed; the pass's number mod 3
+  int nc = 0, ni = 0;                        // candidates listed, and from where they are ions
+  int p3 = 0, half = 0;                      // the pass's number mod 3, and mod 2 (times kTile)
+  bool walls = false;                        // the pass before left its absorbed ions
   const int ci = (tid + T / 2) & (T - 1);    // the wavefronts that do not solve the field first
   uint32_t entry = 0;
   Cold<R> cr = {};
@@ -1806,6 +1851,12 @@ __device__ __forceinline__ void fused_block(const KArgs<R>& A, int b, int G, int
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         if (k0 + q >= end) f.x[q] = (R)-1;
+    }
+    if (s && t - G < te && t != b) {         // ions list their candidates from a whole wavefront on
+      const int at = nc + tid;
+      nc = (nc + 63) & ~63;
+      if (at < nc) L.cxu[at] = XU<R>{(R)-1, (R)0};
+      ni = nc;
     }
     // the pass's candidates join the list: the living that are due for
     // examination (most of them are still there after the push)
@@ -1832,8 +1883,13 @@ __device__ __forceinline__ void fused_block(const KArgs<R>& A, int b, int G, int
     }
     __syncthreads();
     nc += (int)sh.qn[p3];
-    p3 = p3 == 2 ? 0 : p3 + 1;               // the entry of the pass after the next is the one before this
-    if (tid == 0) sh.qn[p3 == 2 ? 0 : p3 + 1] = 0;
+    if (!s) ni = nc;
+    const int next3 = p3 == 2 ? 0 : p3 + 1, last3 = 3 - p3 - next3;
+    if (walls) fused_walls<R>(A, L.wall + (half ^ kTile), (int)sh.wn[last3], buf);   // of the pass before
+    if (tid == 0) {
+      sh.qn[last3] = 0;                      // the pass after the next uses it; all have read it
+      sh.wn[next3] = 0;
+    }
     if (t == b) {
       // a single pass's first candidate of each lane: its record is fetched and
       // its numbers are drawn while the field is solved
@@ -1854,13 +1910,15 @@ __device__ __forceinline__ void fused_block(const KArgs<R>& A, int b, int G, int
     }
     if (!mine) break;
 
-    fused_push<R, kFlux>(A, L, sh, s, k0, N, s ? ion : (R)1, dep_mode, due, at, f, live);
+    fused_push<R, kFlux>(A, L, sh, s, k0, N, s ? ion : (R)1, dep_mode, due, at, L.wall + half, &sh.wn[p3],
+                         f, live);
     {
       R PM_GLOBAL* xs = A.p.xt[s][buf];
       R PM_GLOBAL* us = A.p.ux[s][buf];
       if (k0 + 3 < end) {
-        *(Vec4<R> PM_GLOBAL*)(xs + k0) = f.x;
-        *(Vec4<R> PM_GLOBAL*)(us + k0) = f.u;
+        const int64_t tile = (int64_t)(s ? t - te : t) * kTile;
+        store_tile<R>(xs + tile, f.x);
+        store_tile<R>(us + tile, f.u);
       } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -1877,36 +1935,56 @@ __device__ __forceinline__ void fused_block(const KArgs<R>& A, int b, int G, int
     // kFluxFlushSlots; and the tiles are of one species
     const bool flush = !more || (t + G >= te) != (bool)s ||
                        used == (kFlux ? (int)kFluxFlushSlots : kMaxSlotsPerBlock) / kTile;
-    const bool collide = flush || nc > kFusedList<R> - kTile;
-    if (s || collide) __syncthreads();
-    if (s) fused_walls<R>(A, L, sh, buf);
+    const bool collide = !more || nc > kFusedList<R> - kTile;
+    walls = !(flush || collide);
+    if (!walls) {
+      __syncthreads();
+      fused_walls<R>(A, L.wall + half, (int)sh.wn[p3], buf);
+    }
     if (collide) {
       uint32_t tested = 0;
       for (int r = 0; r < nc; r += T) {      // rounds of one candidate a lane
         const int at = r + ci;
+        const int sc = __builtin_amdgcn_readfirstlane(at) >= ni;   // a wavefront's are of one species
         const XU<R> xu = at < nc ? L.cxu[at] : XU<R>{(R)-1, (R)0};
-        if (xu.x < (R)0) continue;           // absorbed
-        if (!only || r) {
-          record(s, at);
-          draw(s);
+        if (!(xu.x < (R)0)) {                // not absorbed
+          if (!only || r) {
+            record(sc, at);
+            draw(sc);
+          }
+          const bool redraw = (entry >> 31) != 0u;
+          tested += !redraw;
+          mcc_candidate<R>(fresh_case<R>(A), sc, (int64_t)(entry & 0x7FFFFFFFu), redraw, buf, l, xu.x, xu.u, cr.uy,
+                           cr.uz, cr.id, Uniforms8<R>(words), Qn, count_cells ? A.g.cell_count : nullptr, sh.cnt, born,
+                           range_e, range_i);
         }
-        const bool redraw = (entry >> 31) != 0u;
-        tested += !redraw;
-        mcc_candidate<R>(fresh_case<R>(A), s, (int64_t)(entry & 0x7FFFFFFFu), redraw, buf, l, xu.x, xu.u, cr.uy, cr.uz,
-                         cr.id, Uniforms8<R>(words), Qn, count_cells ? A.g.cell_count : nullptr, sh.cnt, born, range_e,
-                         range_i);
+        if (r + T >= nc || r + T + ci >= ni) {   // the wavefront's last of the species
+          if (tested) atomicAdd(&sh.cnt[CN_CAND + sc], tested);
+          tested = 0;
+        }
       }
-      if (tested) atomicAdd(&sh.cnt[CN_CAND + s], tested);
-      nc = 0;
+      nc = ni = 0;
     }
     if (flush) {
-      flush_tile(L.dep, Qn + s * nodes, N, count_cells ? A.g.cell_count + s * N : nullptr);
+      // one atomic a node: the right part of the cell before it and the left of its own
+      for (int m = tid; m < nodes; m += T) {
+        const uint64_t below = m > 0 ? L.dep[m - 1] : 0ull, own = m < N ? L.dep[m] : 0ull, part = (1ull << 48) - 1;
+        const uint64_t q = (own >> 48 << 32) - (own & part) + (below & part);
+        if (q) atomicAdd((unsigned long long*)&Qn[s * nodes + m], (unsigned long long)q);
+        if (count_cells && own) atomicAdd(&A.g.cell_count[s * N + m], (uint32_t)(own >> 48));
+      }
       if (kFlux) flush_flux(L.flux, A.g.sumF + ((int64_t)(pb >= 0 ? pb : 0) * 2 + s) * 2 * nodes, nodes);
       used = 0;
+      if (more) {
+        __syncthreads();
+        for (int m = tid; m < N; m += T) L.dep[m] = 0ull;
+      }
     }
     if (!more) break;
-    t += G;
     if (collide) __syncthreads();            // the list is read
+    t += G;
+    p3 = next3;
+    half ^= kTile;
   }
 
   if (b == 0 && tid == T - 1) {
@@ -1939,9 +2017,9 @@ void k_fused(KArgs<R> args, int i, int i3, int count_cells) {
 
 // A fused step of a batch (no flux profiles there): the workgroups of the work
 // list, as in k_step_batch.  Measured, us a step, two launches -> fused: 64
-// discharges of the sweep in 3 lanes 97.3 -> 86.7, in one 98.6 -> 98.3; 12 of them
-// in a slotted batch, 2 lanes, 32.3 -> 21; 3 in one lane 23.7 -> 13.0; 32 in FP64,
-// 3 lanes, 92.1 -> 79.7.
+// discharges of the sweep in 3 lanes 97.3 -> 82.0, in one 98.6 -> 94.0; 12 of them
+// in a slotted batch, 2 lanes, 32.3 -> 19.1; before the last steps here also 3 in
+// one lane 23.7 -> 13.0 and 32 in FP64, 3 lanes, 92.1 -> 79.7.
 template <typename R>
 __global__ __launch_bounds__(kFusedThreads<R>) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 4 : 2)))
 void k_fused_batch(uintptr_t cases, const uint32_t* __restrict__ work, const uint32_t* __restrict__ nblocks, int i,
