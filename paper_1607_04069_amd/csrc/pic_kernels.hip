@@ -1616,6 +1616,13 @@ __device__ __forceinline__ int one_cell(const int (&key)[4]) {
   return __all(same) ? k : -2;
 }
 
+// A charge share in units of 2^-32 particle: in FP64 one within 2^-33 of the next
+// node is a whole particle, 2^32; in FP32 the largest is 2^32 - 256.
+template <typename R>
+struct ShareOf { using type = uint64_t; };
+template <>
+struct ShareOf<float> { using type = uint32_t; };
+
 // Push of a wavefront's 256 particles, s uniform.  The arithmetic is that of
 // advance(), written out so that it rounds alike wherever it is compiled, and
 // without branches: what leaves the gap, and candidates, are looked at
@@ -1690,13 +1697,14 @@ __device__ __forceinline__ void fused_push(const KArgs<R>& A, const FusedLds<R>&
   }
   // the charge: all four particles of all lanes in one cell (sorted ions) are
   // summed by DPP and added once, otherwise each particle adds to its cell
-  uint32_t W[4];
+  using Share = typename ShareOf<R>::type;
+  Share W[4];
   int key[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int jn = (int)xn[q];
     key[q] = in[q] ? jn : -1;
-    W[q] = in[q] ? (uint32_t)frac_fixed(xn[q] - (R)jn) : 0u;
+    W[q] = in[q] ? (Share)frac_fixed(xn[q] - (R)jn) : (Share)0;
     f.x[q] = in[q] ? xn[q] : (R)-1;
   }
   const int k = dep_mode != 0 ? one_cell(key) : -2;
@@ -1704,8 +1712,8 @@ __device__ __forceinline__ void fused_push(const KArgs<R>& A, const FusedLds<R>&
     uint32_t lo = 0, hi = 0, n = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      lo += W[q] & 0xFFFFu;
-      hi += W[q] >> 16;
+      lo += (uint32_t)(W[q] & 0xFFFFu);
+      hi += (uint32_t)(W[q] >> 16);          // at most 2^16: the sum of 256 stays below 2^25
       n += (uint32_t)__popcll(__ballot(in[q]));
     }
     const uint32_t a = dpp_wave_sum(lo), b = dpp_wave_sum(hi);
