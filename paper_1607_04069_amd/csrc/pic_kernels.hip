@@ -1904,12 +1904,19 @@ __device__ __forceinline__ void fused_block(const KArgs<R>& A, int b, int G, int
       const bool early = only && ci < nc;
       if (early) record(s, ci);
       if (solves) {
-        double num = 0.0, den = 0.0;
+        // behind a blocking capacitor the first launch takes the potential that the
+        // published field was solved at: the load's is the source voltage itself,
+        // which the formula meets only up to rounding
+        double V = next.vs, num = 0.0, den = 0.0;
         if (c.cb > 0.0) {
-          num = S->sigma_init + c.cb * next.vs + c.e_w * (double)n_net;
-          den = c.cgap + c.cb;
+          if (i == 0) {
+            V = S->phi0;
+          } else {
+            num = S->sigma_init + c.cb * next.vs + c.e_w * (double)n_net;
+            den = c.cgap + c.cb;
+          }
         }
-        fused_solve<R>(c, L.q, next.vs, L.E, L.Ep, sh.wq, sh.wd, num, den, &sh.phi0, [&]() {
+        fused_solve<R>(c, L.q, V, L.E, L.Ep, sh.wq, sh.wd, num, den, &sh.phi0, [&]() {
           if (early) draw(s);
         });
         __syncthreads();
