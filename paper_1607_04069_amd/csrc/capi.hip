@@ -194,9 +194,17 @@ int resident_fused_blocks(bool fp64, int N, bool flux, bool batch) {
   return per_cu * cus;
 }
 
-// Passes of a fused step over the initial particles.
-int fused_tiles_of(const pm_case_params* p) {
-  return p->fp64 ? pm::fused_tiles<double>(p->np_e, p->np_i) : pm::fused_tiles<float>(p->np_e, p->np_i);
+// The most workgroups a case's fused steps are worth: one for each pass over the
+// initial particles, and one for every eight passes over the capacity, for a
+// population that outgrows its load.  (5k + 5k particles on 256 cells, a capacity of
+// 640k + 640k and 64 times the load in it, us a step: two launches 161, fused with the
+// workgroups of the load 170, with these 49.  With up to 16 times the load the fused
+// step is the faster either way, and a capacity of at most eight times changes nothing.)
+int fused_groups_of(const pm_case_params* p) {
+  auto tiles = [&](int64_t n_e, int64_t n_i) {
+    return p->fp64 ? pm::fused_tiles<double>(n_e, n_i) : pm::fused_tiles<float>(n_e, n_i);
+  };
+  return std::max(tiles(p->np_e, p->np_i), tiles(p->capacity_e, p->capacity_i) / 8);
 }
 
 bool valid_shape(const pm_launch_shape* s) {
@@ -429,7 +437,7 @@ int sort_grid_for(const pm_case_params* p) {
 // the 978 of one pass each.)  Per-workgroup timestamps are taken of the two
 // launches only.
 int fused_grid_for(const pm_case_params* p, const pm::CaseConst& c) {
-  return c.prof ? 0 : std::min(fused_tiles_of(p), resident_fused_blocks(p->fp64, p->n_cells, c.flux != 0, false));
+  return c.prof ? 0 : std::min(fused_groups_of(p), resident_fused_blocks(p->fp64, p->n_cells, c.flux != 0, false));
 }
 
 // Fewer steps than this up to a sort or the end of the call go by the two
@@ -1511,7 +1519,7 @@ pm_status write_tables(pm_batch* b, hipStream_t st) {
     double lane_work = 0.0;
     for (int k = 0; k < m; ++k) {
       const pm_case* c = b->cases[mem[k]];
-      ft[k] = std::min(fused_tiles_of(&c->prm), 1 << 15);
+      ft[k] = std::min(fused_groups_of(&c->prm), 1 << 15);
       wt[k] = fused_work_of(&c->prm, c->c);
       lane_work += wt[k];
     }
