@@ -424,16 +424,17 @@ pm_status pm_get_step_profile(pm_case* c, uint64_t* out, int64_t cap, int32_t* g
  * How the step kernels (push, collisions, sort) are launched.  The shape changes
  * speed only: every shape computes the same particles (by id), charges and
  * diagnostics, because the random numbers depend on (seed, case_id, particle
- * id, step) and the charge sums are integers.  unroll, waves and work_groups
- * shape the push launch of a single step; several steps in one call choose their
- * own grid. */
+ * id, step) and the charge sums are integers.  unroll and waves shape the push
+ * launch of a single step; the launches of several steps in one call have a form
+ * of their own. */
 typedef struct {
   int32_t unroll;         /* particles per lane in flight: 8 or 16                      */
   int32_t waves;          /* register budget of the push kernel: 0 the compiler's own,  */
                           /* 6 at most 80 VGPRs so that six waves fit per SIMD         */
   int32_t work_groups;    /* workgroups that share the particles (a case: at most one   */
                           /* per 256 initial particles; a batch: over all its cases);   */
-                          /* 0 = one resident wave of the device                        */
+                          /* 0 = one resident wave of the device.  Several steps in one */
+                          /* call use at most as many (a batch at least one per case)   */
   int32_t deposit_mode;   /* charge into the LDS tile: 0 an atomic per particle, 1 a    */
                           /* wavefront in one cell summed by DPP, per-particle atomics */
                           /* otherwise                                                 */
@@ -443,7 +444,7 @@ typedef struct {
                           /* case: ignored (reported as 1)                             */
 } pm_launch_shape;
 
-/* The case's shape; work_groups is the count in effect. */
+/* The case's shape; work_groups is the count in effect for single steps. */
 pm_status pm_get_launch_shape(const pm_case* c, pm_launch_shape* out);
 
 /* Change the case's shape (PM_EINVAL for values outside the ranges above; a

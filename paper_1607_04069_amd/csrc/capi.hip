@@ -434,10 +434,12 @@ int sort_grid_for(const pm_case_params* p) {
 // device at once, passes in turn beyond that.  (Every workgroup solves the field
 // for itself, so a second generation of them costs more than a second pass:
 // 1M + 1M particles, 1024 cells, a step in 24.5 us with 512 workgroups, 30.7 with
-// the 978 of one pass each.)  Per-workgroup timestamps are taken of the two
-// launches only.
-int fused_grid_for(const pm_case_params* p, const pm::CaseConst& c) {
-  return c.prof ? 0 : std::min(fused_groups_of(p), resident_fused_blocks(p->fp64, p->n_cells, c.flux != 0, false));
+// the 978 of one pass each.)  limit: the caller's, 0 for none.  Per-workgroup
+// timestamps are taken of the two launches only.
+int fused_grid_for(const pm_case_params* p, const pm::CaseConst& c, int limit) {
+  if (c.prof) return 0;
+  const int g = std::min(fused_groups_of(p), resident_fused_blocks(p->fp64, p->n_cells, c.flux != 0, false));
+  return limit > 0 ? std::min(g, limit) : g;
 }
 
 // Fewer steps than this up to a sort or the end of the call go by the two
@@ -973,7 +975,7 @@ pm_status pm_init_case(const pm_case_params* p, void* arena, size_t bytes, void*
   c->mcc_grid = mcc_grid_for(
       p, c->c, mcc_per_lane(expected_candidates(p, c->c), resident_mcc_blocks(p->fp64, p->n_cells, false)));
   c->sort_grid = sort_grid_for(p);
-  c->fused_grid = fused_grid_for(p, c->c);
+  c->fused_grid = fused_grid_for(p, c->c, 0);
   c->cap_stream = nullptr;
   c->graph = nullptr;
   c->exec = nullptr;
@@ -1182,6 +1184,7 @@ pm_status pm_set_launch_shape(pm_case* c, const pm_launch_shape* sh, void* strea
       ? std::min(sh->work_groups, most)
       : work_grid_for(&c->prm, resident_step_blocks(c->prm.fp64, c->c.N, sh->unroll, sh->waves, false));
   c->step_grid = std::max(c->work_grid, slot_grid_for(&c->prm));
+  c->fused_grid = fused_grid_for(&c->prm, c->c, sh->work_groups);
   fill_args<float>(c->af, c->c, c->arena, c->map);
   fill_args<double>(c->ad, c->c, c->arena, c->map);
   if (c->prm.fp64) PM_TRY(hipMemcpyAsync(c->arena + c->map.args, &c->ad, sizeof(c->ad), hipMemcpyHostToDevice, st));
@@ -1462,8 +1465,10 @@ pm_status write_tables(pm_batch* b, hipStream_t st) {
   // discharges in 3 lanes 99.9 -> 86.7 us a step, 16 in 2 lanes 28.0 -> 27.5, 8 in
   // 2 lanes 21.8 -> 16.8; in a single lane the second generation costs more than
   // the balance gives: 98.3 -> 110.9)
+  const int64_t most_fused = b->shape.work_groups > 0 ? b->shape.work_groups : max_resident_blocks();
   const int64_t resident_fused = std::min<int64_t>(
-      (int64_t)resident_fused_blocks(b->fp64, b->maxN, false, true) * (nl > 1 ? 3 : 2) / 2, max_resident_blocks());
+      {(int64_t)resident_fused_blocks(b->fp64, b->maxN, false, true) * (nl > 1 ? 3 : 2) / 2, most_fused,
+       (int64_t)max_resident_blocks()});
   const int64_t lane_fused = std::max<int64_t>(resident_fused / nl, (n + nl - 1) / nl);
   double fused_work = 0.0;
   bool fused = true;
