@@ -5,11 +5,13 @@ budget, workgroups sharing the particles, LDS deposit variant, steps between
 cell sorts) computes the same particles, charges and diagnostics; only the
 speed differs.  The tuner therefore times candidate shapes on the live state --
 the steps it takes are real steps of the run -- and keeps the fastest, in
-stages: kernel variant and workgroup count (and, for a batch, lanes), a runoff
-of the best few of those re-timed in alternation, then deposit variant, then
-sort interval.  Choices are cached in a JSON file keyed by the device and a
-signature of the workload, so a later run of the same workload starts from the
-tuned shape without timing anything.
+stages, each timed by the calls that its fields act on: push variant and
+workgroup count by single steps, with a runoff of the best few re-timed in
+alternation; then, by calls of several steps, a batch's lanes, the deposit
+variant and the sort interval.  The workgroup counts tried are those that leave
+calls of several steps their full resident wave.  Choices are cached in a JSON
+file keyed by the device and a signature of the workload, so a later run of the
+same workload starts from the tuned shape without timing anything.
 """
 import json
 import math
@@ -17,6 +19,9 @@ import os
 import time
 
 CACHE_ENV = "PICMCC_TUNE_CACHE"
+# part of the key: a call of several steps takes one launch a step (shapes chosen
+# when it took two are not looked up)
+STEP_FORM = "one-launch"
 
 
 def cache_path():
@@ -80,22 +85,31 @@ class _Target:
     def particle_steps(self):
         return sum(c.sample_diagnostics()["particle_steps"] for c in self.cases)
 
-    def rate(self, steps):
+    def rate(self, steps, single=False):
+        """Particle-steps/s of a call of several steps, or of as many calls of one."""
         import torch
         torch.cuda.synchronize()
         p0 = self.particle_steps()
         t0 = time.perf_counter()
-        self.obj.step(steps)
+        if single:
+            for _ in range(steps):
+                self.obj.step(1)
+        else:
+            self.obj.step(steps)
         torch.cuda.synchronize()
         dt = time.perf_counter() - t0
         return (self.particle_steps() - p0) / dt
+
+
+def workload_key(obj, params):
+    return "|".join((_device(), "batch" if hasattr(obj, "cases") else "case", STEP_FORM, signature(params)))
 
 
 def tune(obj, params, steps=None, use_cache=True, log=None):
     """Tune the launch shape of a Case or Batch (params: the parameter dicts of
     its cases) and leave the best shape set.  Returns (shape, particle-steps/s,
     source) with source "cache" or "timed"."""
-    key = _device() + "|" + ("batch" if hasattr(obj, "cases") else "case") + "|" + signature(params)
+    key = workload_key(obj, params)
     if use_cache:
         hit = _load().get(key)
         if hit:
@@ -106,28 +120,21 @@ def tune(obj, params, steps=None, use_cache=True, log=None):
     obj.set_launch_shape(work_groups=0)
     resident = obj.launch_shape()["work_groups"]
     is_batch = hasattr(obj, "cases")
-    mults = (1, 2, 3) if is_batch else (0.25, 0.5, 1)
+    mults = (1, 2, 3) if is_batch else (0.5, 1)
     sort0 = base["sort_interval"] or 25
     if steps is None:
         steps = 200 if is_batch else 100
     steps = sort0 * max(1, -(-steps // sort0))     # whole sort intervals per trial
-    best = None
 
-    tried = []                                       # (shape, rate) of every trial
-
-    def trial(**kw):
-        nonlocal best
+    def trial(single, **kw):
         obj.set_launch_shape(**kw)
         obj.step(4)                                  # settle caches after the change
-        r = max(t.rate(steps), t.rate(steps))        # the better of two, against transients
+        r = max(t.rate(steps, single), t.rate(steps, single))   # the better of two, against transients
         if log:
-            log(f"  shape {kw}: {r:.3e} particle-steps/s")
-        tried.append((obj.launch_shape(), r))
-        if best is None or r > best[1]:
-            best = (obj.launch_shape(), r)
-        return r
+            log(f"  shape {kw}{', single steps' if single else ''}: {r:.3e} particle-steps/s")
+        return obj.launch_shape(), r
 
-    def runoff(k=3, rounds=2):
+    def runoff(tried, single, k=3, rounds=2):
         """Re-time the k best distinct shapes so far in alternation: the state
         evolves during the search, so trials taken at different times are not
         quite comparable; alternating shapes sees the same state for each."""
@@ -142,44 +149,23 @@ def tune(obj, params, steps=None, use_cache=True, log=None):
             for i, (sh, _) in enumerate(uniq):
                 obj.set_launch_shape(**sh)
                 obj.step(4)
-                score[i].append(t.rate(steps))
+                score[i].append(t.rate(steps, single))
         i_best = max(score, key=lambda i: sum(score[i]) / len(score[i]))
         if log:
             for i, (sh, _) in enumerate(uniq):
                 log(f"  runoff {sh}: {sum(score[i]) / len(score[i]):.3e} particle-steps/s")
-        return uniq[i_best][0], sum(score[i_best]) / len(score[i_best])
+        return uniq[i_best][0]
 
-    # stage 1: kernel variant and workgroups, each trial over whole sort intervals
-    # (a call sorts after every sort_interval-th step) so all see the same mix
-    slots = sum(int(p["np_e"]) + int(p["np_i"]) for p in params)
-    for unroll in (8, 16):
-        for waves in (0, 6):
-            counts = {max(1, int(resident * m)) for m in mults}
-            if not is_batch:
-                # one tile (256 x unroll slots) per workgroup, when that fits a resident wave
-                tiles = -(-slots // (256 * unroll))
-                if tiles <= resident:
-                    counts.add(tiles)
-            for wg in sorted(counts):
-                trial(unroll=unroll, waves=waves, work_groups=wg, deposit_mode=1, sort_interval=sort0, lanes=1)
+    # stage 1: push variant and workgroups of single steps, each trial over whole
+    # sort intervals so all see the same mix
+    shape = dict(runoff([trial(True, unroll=unroll, waves=waves, work_groups=max(1, int(resident * m)), deposit_mode=1,
+                               sort_interval=sort0, lanes=1)
+                         for unroll in (8, 16) for waves in (0, 6) for m in mults], True))
     if is_batch:
-        # stage 1b: lanes stepped concurrently, sharing the workgroups, for the
-        # two best kernel variants of stage 1
-        firsts = []
-        for sh, _ in sorted(tried, key=lambda e: -e[1]):
-            if (sh["unroll"], sh["waves"]) not in [(f["unroll"], f["waves"]) for f in firsts]:
-                firsts.append(sh)
-        for first in firsts[:2]:
-            for lanes in (2, 3, 4):
-                for m in (0.5, 1, 2):
-                    trial(**dict(first, lanes=lanes, work_groups=max(1, int(first["work_groups"] * m))))
-    # the best few variant / workgroup / lane combinations re-timed side by side
-    shape = dict(runoff()[0])
+        # stage 1b: lanes stepped concurrently
+        shape = dict(runoff([trial(False, **dict(shape, lanes=lanes)) for lanes in (1, 2, 3, 4)], False))
     # stage 2: deposit variant
-    best = (shape, 0.0)
-    for dm in (1, 0):
-        trial(**dict(shape, deposit_mode=dm))
-    shape = dict(best[0])
+    shape = dict(max((trial(False, **dict(shape, deposit_mode=dm)) for dm in (1, 0)), key=lambda e: e[1])[0])
     # stage 3: sort interval, timed over several intervals
     best = None
     long_steps = 200 if is_batch else 100
