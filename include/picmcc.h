@@ -335,7 +335,8 @@ pm_status pm_inject_sputtered(pm_case* c, const pm_sputter_params* sp, pm_tp_sou
                               void* hip_stream);
 
 /* Fly source->n_atoms test atoms to the walls (Sec. IV.B) with tallies in an
- * arena of pm_tp_footprint bytes.  Synchronises; fills *out. */
+ * arena of pm_tp_footprint bytes.  Synchronises; fills *out.  PM_EDEVICE too if
+ * the counts at the walls and in the gas do not add up to n_atoms. */
 pm_status pm_run_test_particles(const pm_tp_params* tp, const pm_tp_source* src,
                                 void* dev_arena, size_t arena_bytes, void* hip_stream,
                                 pm_tp_result* out);

@@ -919,7 +919,7 @@ pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, hi
     }
   if (!whole) PM_TRY(hipStreamSynchronize(st));
   out->n_substrate = (int64_t)h.n_sub;
-  out->n_target = src->n_atoms - (int64_t)h.n_sub - (int64_t)h.n_unf;
+  out->n_target = (int64_t)h.n_tgt;
   out->n_unfinished = (int64_t)h.n_unf;
   out->events = h.sum[2];
   out->collisions = h.sum[3];
@@ -929,7 +929,8 @@ pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, hi
   out->eta = src->n_atoms > 0 ? (double)h.n_sub / (double)src->n_atoms : 0.0;
   out->deposition_flux = out->eta * src->flux_m2s;
   out->nu_max = t.nu_max;
-  return PM_OK;
+  // the three counts are taken apart from one another: each atom ends exactly once
+  return out->n_substrate + out->n_target + out->n_unfinished == src->n_atoms ? PM_OK : PM_EDEVICE;
 }
 }  // namespace
 

@@ -83,9 +83,9 @@ struct TpConst {
 
 struct TpTally {              // device tallies (zeroed before a run)
   uint64_t sum[4];             // impact energies at the target, at the substrate (2^-20 eV), events, collisions
-  uint64_t n_sub, n_unf;       // the other atoms ended at the target
+  uint64_t n_sub, n_tgt, n_unf;
   uint64_t overflow;
-  uint64_t pad0[9];
+  uint64_t pad0[8];
   uint64_t next;               // atoms taken by the flight's wavefronts beyond their first runs
   uint64_t pad1[15];
 };

@@ -134,7 +134,7 @@ __device__ __forceinline__ long long rint_i64(float x) {
 // low pressure).
 struct TpShared {
   unsigned long long sum[4][64];        // TpTally's four sums, in its order
-  uint32_t n_unf, over;
+  uint32_t n_tgt, n_unf, over;
 };
 
 struct TpLds {
@@ -310,6 +310,8 @@ __device__ __forceinline__ void finish(const TpConst& T, const TpLds& S, const T
       atomicAdd(&S.e[(int)fminf(fmaxf(E / T.f.ebin, 0.0f), (float)(T.n_ebins - 1))], 1u);
       atomicAdd(&S.th[(int)fminf(fmaxf(th, 0.0f), (float)(kTpThetaBins - 1))], 1u);
       atomicAdd(&S.tof[(int)fminf(fmaxf(tof / T.f.tbin, 0.0f), (float)(T.n_tbins - 1))], 1u);
+    } else {
+      atomicAdd(&S.sh->n_tgt, 1u);
     }
   } else {
     atomicAdd(&S.sh->n_unf, 1u);
@@ -414,7 +416,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_tp_flight(TpConst T, TpTally* tal
   if (T.n_xbins)
     for (int i = tid; i < 4 * nx1; i += kBlock) sP[i] = 0ull;
   sh.sum[tid >> 6][lane] = 0ull;
-  if (tid == 0) sh.n_unf = sh.over = 0;
+  if (tid == 0) sh.n_tgt = sh.n_unf = sh.over = 0;
   __syncthreads();
 
   unsigned long long* next = reinterpret_cast<unsigned long long*>(&tal->next);
@@ -721,6 +723,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_tp_flight(TpConst T, TpTally* tal
     if (n_sub) atomicAdd((unsigned long long*)&tal->n_sub, (unsigned long long)n_sub);
   }
   if (tid == 0) {
+    if (sh.n_tgt) atomicAdd((unsigned long long*)&tal->n_tgt, (unsigned long long)sh.n_tgt);
     if (sh.n_unf) atomicAdd((unsigned long long*)&tal->n_unf, (unsigned long long)sh.n_unf);
     if (sh.over) atomicAdd((unsigned long long*)&tal->overflow, (unsigned long long)sh.over);
   }
