@@ -131,23 +131,27 @@ __device__ __forceinline__ long long rint_i64(float x) {
 // Tallies of one workgroup.  Sums that an ending atom adds to are kept per lane
 // of a wavefront, so that the atoms that end in one pass never meet on one
 // address (summed by a loop over those lanes, they took a fifth of the flight at
-// low pressure).
+// low pressure).  Beside histograms that leave no room for that the lanes share
+// one sum (kCols = 1).
+template <int kCols>
 struct TpShared {
-  unsigned long long sum[4][64];        // TpTally's four sums, in its order
+  unsigned long long sum[4][kCols];     // TpTally's four sums, in its order
   uint32_t n_tgt, n_unf, over;
 };
 
+template <int kCols>
 struct TpLds {
   unsigned long long *pt, *dt, *px, *dd;   // [n_xbins + 1] each
   uint32_t *e, *th, *tof;
-  TpShared* sh;
+  TpShared<kCols>* sh;
 };
 
 // Add a straight flight xa -> xb at x-velocity vx to the LDS profile tallies:
 // partial cells directly (time overlap / |vx|, displacement overlap * sign), the
 // cells crossed end to end as a difference (+ at the first, - past the last) of
 // their common time dx / |vx| and displacement dx * sign, summed up at the end.
-__device__ __forceinline__ void track_tally(const TpConst& T, const TpLds& S, float xa, float xb, float vx) {
+template <int kCols>
+__device__ __forceinline__ void track_tally(const TpConst& T, const TpLds<kCols>& S, float xa, float xb, float vx) {
 #pragma clang fp contract(off)   // a cell edge at the wall: the product is rounded before the difference
   if (vx == 0.0f) return;
   const float lo = fminf(xa, xb), hi = fmaxf(xa, xb);
@@ -297,15 +301,17 @@ __device__ __forceinline__ float ratio_bound(const TpConst& T, const Atom& a) {
 
 // Tally an atom that ended at wall (0 target, 1 substrate, 2 in the gas after
 // e_max events) with time of flight tof.
-__device__ __forceinline__ void finish(const TpConst& T, const TpLds& S, const TpTrace& tr, int64_t k, const Atom& a,
-                                       int wall, float tof, uint32_t coll, int lane) {
+template <int kCols>
+__device__ __forceinline__ void finish(const TpConst& T, const TpLds<kCols>& S, const TpTrace& tr, int64_t k,
+                                       const Atom& a, int wall, float tof, uint32_t coll, int lane) {
+  const int col = lane % kCols;
   const float v2 = fmaf(a.vz, a.vz, fmaf(a.vx, a.vx, a.vy * a.vy));
   const float E = T.f.e_half_m * v2;
   const float th = acosf(fminf(fabsf(a.vx) / sqrtf(v2), 1.0f)) * 57.29577951308232f;
-  atomicAdd(&S.sh->sum[2][lane], (unsigned long long)a.e);
-  atomicAdd(&S.sh->sum[3][lane], (unsigned long long)coll);
+  atomicAdd(&S.sh->sum[2][col], (unsigned long long)a.e);
+  atomicAdd(&S.sh->sum[3][col], (unsigned long long)coll);
   if (wall < 2) {
-    atomicAdd(&S.sh->sum[wall][lane], (unsigned long long)rint_i64(E * 1048576.0f));   // E 2^20 is exact in FP32
+    atomicAdd(&S.sh->sum[wall][col], (unsigned long long)rint_i64(E * 1048576.0f));   // E 2^20 is exact in FP32
     if (wall) {
       atomicAdd(&S.e[(int)fminf(fmaxf(E / T.f.ebin, 0.0f), (float)(T.n_ebins - 1))], 1u);
       atomicAdd(&S.th[(int)fminf(fmaxf(th, 0.0f), (float)(kTpThetaBins - 1))], 1u);
@@ -396,14 +402,14 @@ constexpr int kWidest = kFixed ? 6 : 4;
 // fixed-step M1 atoms (2.2e8 steps) 170 -> 8 ms, 1e7 at 0.5 Pa (4.3e7 events)
 // 2.87 -> 1.22 ms (there the one tally call and generator call per pass, the
 // lane-wise sums and the float constants count).
-template <bool kFixed>
+template <bool kFixed, int kCols>
 __global__ __launch_bounds__(kBlock, 6) void k_tp_flight(TpConst T, TpTally* tal, uint64_t* e_hist, uint64_t* th_hist,
                                                          uint64_t* tof_hist, TpTrace tr, int64_t* prof) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ TpShared sh;
+  __shared__ TpShared<kCols> sh;
   const int nx1 = T.n_xbins + 1, tid = threadIdx.x, lane = tid & 63;
   unsigned long long* sP = reinterpret_cast<unsigned long long*>(smem);   // [4][n_xbins + 1]
-  TpLds S;
+  TpLds<kCols> S;
   S.pt = sP;
   S.dt = sP + nx1;
   S.px = sP + 2 * nx1;
@@ -415,7 +421,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_tp_flight(TpConst T, TpTally* tal
   for (int i = tid; i < T.n_ebins + kTpThetaBins + T.n_tbins; i += kBlock) S.e[i] = 0;
   if (T.n_xbins)
     for (int i = tid; i < 4 * nx1; i += kBlock) sP[i] = 0ull;
-  sh.sum[tid >> 6][lane] = 0ull;
+  if (lane < kCols) sh.sum[tid >> 6][lane] = 0ull;
   if (tid == 0) sh.n_tgt = sh.n_unf = sh.over = 0;
   __syncthreads();
 
@@ -715,7 +721,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_tp_flight(TpConst T, TpTally* tal
       if (sP[i]) atomicAdd((unsigned long long*)&prof[i], sP[i]);
   // one sum per wavefront
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  unsigned long long v = sh.sum[w][lane];
+  unsigned long long v = lane < kCols ? sh.sum[w][lane] : 0ull;
   for (int off = 32; off; off >>= 1) v += __shfl_xor(v, off, 64);
   for (int off = 32; off; off >>= 1) n_sub += __shfl_xor(n_sub, off, 64);
   if (lane == 0) {
@@ -851,12 +857,15 @@ hipError_t launch_tp_flight(TpConst T, TpTally* tally, uint64_t* e_hist, uint64_
   T.first_run = (int64_t)grid * (kBlock / 64) * T.run;
   const size_t lds = (size_t)(T.n_ebins + kTpThetaBins + T.n_tbins) * 4 +
                      (T.n_xbins ? (size_t)4 * (T.n_xbins + 1) * 8 : 0);
-  if (fixed)
-    hipLaunchKernelGGL(k_tp_flight<true>, dim3(grid), dim3(kBlock), lds, st, T, tally, e_hist, th_hist, tof_hist,
-                       trace, prof);
+  auto fly = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), lds, st, T, tally, e_hist, th_hist, tof_hist, trace, prof);
+  };
+  // the lane-wise sums (2 KB) where they fit beside the histograms
+  constexpr size_t kLdsPerGroup = 160 * 1024;
+  if (lds + sizeof(TpShared<64>) <= kLdsPerGroup)
+    fixed ? fly(k_tp_flight<true, 64>) : fly(k_tp_flight<false, 64>);
   else
-    hipLaunchKernelGGL(k_tp_flight<false>, dim3(grid), dim3(kBlock), lds, st, T, tally, e_hist, th_hist, tof_hist,
-                       trace, prof);
+    fixed ? fly(k_tp_flight<true, 1>) : fly(k_tp_flight<false, 1>);
   return hipGetLastError();
 }
 
