@@ -6,6 +6,8 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
+#include <mutex>
 #include <new>
 #include <type_traits>
 #include <vector>
@@ -768,7 +770,7 @@ struct TpLayout {
   size_t tally, e_hist, th_hist, tof_hist, prof, prof_out, total;
 };
 
-// The most that a flight's results are read back through the stack.
+// The most that a flight's results are read back in one copy.
 constexpr size_t kTpReadBytes = 64 * 1024;
 
 TpLayout tp_layout(const pm_tp_params* tp) {
@@ -802,10 +804,11 @@ pm_status tp_validate(const pm_tp_params* tp, const pm_tp_source* src) {
 }
 
 // The flight of src->n_atoms atoms with its tallies at base (tp_layout bytes,
-// 256-byte aligned); fills *out from there.  Allocates nothing: the device
-// buffers are the caller's, the read-outs go straight into the caller's host
-// arrays and a struct on the stack.  Synchronises the stream.
-pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, hipStream_t st, pm_tp_result* out) {
+// 256-byte aligned); fills *out from there.  Allocates nothing: the device buffers
+// are the caller's, and the results come through host (tp_layout bytes), or without
+// it (null) straight into the caller's arrays.  Synchronises the stream.
+pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, char* host, hipStream_t st,
+                 pm_tp_result* out) {
   const double m = tp->m_test_amu * kAmu, M = tp->m_gas_amu * kAmu;
   const double mr = m * M / (m + M);
   const double n_gas = tp->p_pa / (kKB * tp->t_gas_k);
@@ -892,17 +895,15 @@ pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, hi
     const double per_atom = src->flux_m2s / (double)std::max<int64_t>(src->n_atoms, 1);
     PM_TRY(pm::launch_tp_profiles(prof, nx, t.xbin, per_atom, pout, st));
   }
-  // The results come back in one copy where they fit on the stack (40 KB with the
-  // usual bins; a flight of 10k atoms 254 -> 144 us), else one by one: each of the
-  // eight copies into pageable memory costs as much as 40 KB.
-  alignas(16) char host[kTpReadBytes];
-  const bool whole = L.total <= sizeof(host);
-  if (whole) {
+  // The results come back in one copy where there is a host buffer for them (40 KB
+  // with the usual bins; a flight of 10k atoms 254 -> 144 us), else one by one: each
+  // of the eight copies into pageable memory costs as much as 40 KB.
+  if (host) {
     PM_TRY(hipMemcpyAsync(host, base, L.total, hipMemcpyDeviceToHost, st));
     PM_TRY(hipStreamSynchronize(st));
   }
   auto read = [&](void* dst, const void* src_dev, size_t bytes) {
-    if (!whole) return hipMemcpyAsync(dst, src_dev, bytes, hipMemcpyDeviceToHost, st);
+    if (!host) return hipMemcpyAsync(dst, src_dev, bytes, hipMemcpyDeviceToHost, st);
     std::memcpy(dst, host + (static_cast<const char*>(src_dev) - base), bytes);
     return hipSuccess;
   };
@@ -917,7 +918,7 @@ pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, hi
       if (nx) PM_TRY(read(dst[q], pout + (size_t)q * nx, (size_t)nx * 8));
       else std::memset(dst[q], 0, (size_t)tp->n_xbins * 8);    // no profiles in a periodic box
     }
-  if (!whole) PM_TRY(hipStreamSynchronize(st));
+  if (!host) PM_TRY(hipStreamSynchronize(st));
   out->n_substrate = (int64_t)h.n_sub;
   out->n_target = (int64_t)h.n_tgt;
   out->n_unfinished = (int64_t)h.n_unf;
@@ -1274,7 +1275,9 @@ pm_status pm_run_test_particles(const pm_tp_params* tp, const pm_tp_source* src,
   const pm_status v = tp_validate(tp, src);
   if (v != PM_OK) return v;
   if (bytes < pm_tp_footprint(tp)) return PM_ENOSPACE;
-  return tp_run(tp, src, reinterpret_cast<char*>(arena), as_stream(stream), out);
+  const size_t need = pm_tp_footprint(tp);
+  std::unique_ptr<char[]> host(need <= kTpReadBytes ? new (std::nothrow) char[need] : nullptr);
+  return tp_run(tp, src, reinterpret_cast<char*>(arena), host.get(), as_stream(stream), out);
 }
 
 pm_status pm_run_test_particles_static(const pm_tp_params* tp, const pm_tp_source* src, void* stream,
@@ -1285,7 +1288,12 @@ pm_status pm_run_test_particles_static(const pm_tp_params* tp, const pm_tp_sourc
   if (pm_tp_footprint(tp) > pm::kTpScratchBytes) return PM_ENOSPACE;
   void* base = nullptr;
   PM_TRY(pm::tp_scratch(&base));
-  return tp_run(tp, src, reinterpret_cast<char*>(base), as_stream(stream), out);
+  // one host buffer for the call that has it; another GPU's call at the same time goes without
+  static std::mutex mu;
+  alignas(16) static char host[kTpReadBytes];
+  const std::unique_lock<std::mutex> held(mu, std::try_to_lock);
+  char* to = held.owns_lock() && pm_tp_footprint(tp) <= kTpReadBytes ? host : nullptr;
+  return tp_run(tp, src, reinterpret_cast<char*>(base), to, as_stream(stream), out);
 }
 
 }  // extern "C"
