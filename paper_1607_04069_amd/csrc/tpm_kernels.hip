@@ -843,13 +843,16 @@ hipError_t tp_scratch(void** ptr) {
 // step, whose lanes all count, twice as many: 1e5 atoms 7.9 ms against 9.3).
 hipError_t launch_tp_flight(TpConst T, TpTally* tally, uint64_t* e_hist, uint64_t* th_hist, uint64_t* tof_hist,
                             TpTrace trace, int64_t* prof, hipStream_t st) {
-  constexpr int64_t kWaves = 256 * 4 * 4;
+  int dev = 0, cus = 0;
+  (void)hipGetDevice(&dev);
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 1;
+  const int64_t most = (int64_t)cus * 4 * 4;
   const bool fixed = T.dt > 0.0;
   const int widest = fixed ? kWidest<true> : kWidest<false>;
   T.wlog = 0;
-  while (T.wlog < widest && T.n_atoms <= (fixed ? 128 : 64) * kWaves >> (T.wlog + 1)) ++T.wlog;
+  while (T.wlog < widest && T.n_atoms <= (fixed ? 128 : 64) * most >> (T.wlog + 1)) ++T.wlog;
   const int64_t per_wave = 64 >> T.wlog;
-  const int64_t waves = std::min((T.n_atoms + per_wave - 1) / per_wave, kWaves);
+  const int64_t waves = std::min((T.n_atoms + per_wave - 1) / per_wave, most);
   const int grid = (int)std::max<int64_t>(1, (waves + kBlock / 64 - 1) / (kBlock / 64));
   // eight runs per wavefront: the atomics on the queue stay rare and the runs of
   // the last ones short
