@@ -18,6 +18,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 
 #include "philox.h"
@@ -835,6 +836,19 @@ hipError_t tp_scratch(void** ptr) {
   return hipSuccess;
 }
 
+// Compute units of the current device.  Asked for once per device: the query costs
+// a few microseconds, of the 140 of a short flight.
+static int compute_units() {
+  static std::atomic<int> known[kMaxDevices];
+  int dev = 0, cus = 0;
+  (void)hipGetDevice(&dev);
+  const bool kept = dev >= 0 && dev < kMaxDevices;
+  if (kept && (cus = known[dev].load(std::memory_order_relaxed)) > 0) return cus;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) return 1;
+  if (kept) known[dev].store(cus, std::memory_order_relaxed);
+  return cus;
+}
+
 // Lanes per atom and atoms per run of the flight.  Four wavefronts per SIMD keep
 // the vector ALU busy and leave fewer atoms in flight when the queue runs dry
 // than the six to eight that fit (1e6 atoms at 5 Pa: 9.3 ms, 10.3 with six, 9.8
@@ -843,10 +857,7 @@ hipError_t tp_scratch(void** ptr) {
 // step, whose lanes all count, twice as many: 1e5 atoms 7.9 ms against 9.3).
 hipError_t launch_tp_flight(TpConst T, TpTally* tally, uint64_t* e_hist, uint64_t* th_hist, uint64_t* tof_hist,
                             TpTrace trace, int64_t* prof, hipStream_t st) {
-  int dev = 0, cus = 0;
-  (void)hipGetDevice(&dev);
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 1;
-  const int64_t most = (int64_t)cus * 4 * 4;
+  const int64_t most = (int64_t)compute_units() * 4 * 4;
   const bool fixed = T.dt > 0.0;
   const int widest = fixed ? kWidest<true> : kWidest<false>;
   T.wlog = 0;
