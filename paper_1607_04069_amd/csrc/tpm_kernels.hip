@@ -709,12 +709,8 @@ __global__ __launch_bounds__(kBlock, 6) void k_tp_flight(TpConst T, TpTally* tal
   __syncthreads();
   for (int i = tid; i < T.n_ebins; i += kBlock)
     if (S.e[i]) atomicAdd((unsigned long long*)&e_hist[i], (unsigned long long)S.e[i]);
-  uint32_t n_sub = 0;
   for (int i = tid; i < kTpThetaBins; i += kBlock)
-    if (S.th[i]) {
-      n_sub = S.th[i];                                     // every atom at the substrate has an angle
-      atomicAdd((unsigned long long*)&th_hist[i], (unsigned long long)n_sub);
-    }
+    if (S.th[i]) atomicAdd((unsigned long long*)&th_hist[i], (unsigned long long)S.th[i]);
   for (int i = tid; i < T.n_tbins; i += kBlock)
     if (S.tof[i]) atomicAdd((unsigned long long*)&tof_hist[i], (unsigned long long)S.tof[i]);
   if (T.n_xbins && prof)
@@ -724,10 +720,15 @@ __global__ __launch_bounds__(kBlock, 6) void k_tp_flight(TpConst T, TpTally* tal
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   unsigned long long v = lane < kCols ? sh.sum[w][lane] : 0ull;
   for (int off = 32; off; off >>= 1) v += __shfl_xor(v, off, 64);
-  for (int off = 32; off; off >>= 1) n_sub += __shfl_xor(n_sub, off, 64);
-  if (lane == 0) {
-    if (v) atomicAdd((unsigned long long*)&tal->sum[w], v);
-    if (n_sub) atomicAdd((unsigned long long*)&tal->n_sub, (unsigned long long)n_sub);
+  if (lane == 0 && v) atomicAdd((unsigned long long*)&tal->sum[w], v);
+  // every atom at the substrate has an angle.  (The workgroups of a short flight end
+  // together and their atomics on the tallies take turns: one more each costs 10007
+  // atoms at 0.5 Pa 4 us of 140.)
+  if (w == 0) {
+    uint32_t n_sub = 0;
+    for (int i = lane; i < kTpThetaBins; i += 64) n_sub += S.th[i];
+    for (int off = 32; off; off >>= 1) n_sub += __shfl_xor(n_sub, off, 64);
+    if (lane == 0 && n_sub) atomicAdd((unsigned long long*)&tal->n_sub, (unsigned long long)n_sub);
   }
   if (tid == 0) {
     if (sh.n_tgt) atomicAdd((unsigned long long*)&tal->n_tgt, (unsigned long long)sh.n_tgt);
