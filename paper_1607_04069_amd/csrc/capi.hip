@@ -821,54 +821,38 @@ pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, ch
                          std::tgamma(2.5 - tp->omega);
   pm::TpConst t;
   std::memset(&t, 0, sizeof(t));
-  t.L = tp->gap_m;
-  t.lat = tp->lateral_m;
-  t.nu_max = n_gas * sig_cap * g_cap;
-  t.inv_nu_max = t.nu_max > 0 ? 1.0 / t.nu_max : INFINITY;
-  t.sg_exp = 2.0 - 2.0 * tp->omega;
-  t.log2_gcap = std::log2(g_cap);
-  t.sig_gas = std::sqrt(kKB * tp->t_gas_k / M);
-  t.m_ratio = m / (m + M);
-  t.M_ratio = M / (m + M);
-  t.s_max = src->e_cut_ev / (src->e_cut_ev + src->u_s_ev);
-  t.u_s = src->u_s_ev;
-  t.v_per_sqrt_ev = std::sqrt(2.0 * kE / m);
-  t.e_half_m = 0.5 * m / kE;
-  t.ebin = tp->ebin_ev;
-  t.tbin = tp->tbin_s;
+  const double nu_max = n_gas * sig_cap * g_cap;
+  const double xbin = tp->gap_m / std::max(tp->n_xbins, 1);
+  t.f.L = (float)tp->gap_m;
+  t.f.inv_L = (float)(1.0 / tp->gap_m);
+  t.f.inv_nu = nu_max > 0 ? (float)(1.0 / nu_max) : INFINITY;
+  t.f.sig_gas = (float)std::sqrt(kKB * tp->t_gas_k / M);
+  t.f.m_ratio = (float)(m / (m + M));
+  t.f.M_ratio = (float)(M / (m + M));
+  t.f.sg_exp = (float)(2.0 - 2.0 * tp->omega);
+  t.f.log2_gcap = (float)std::log2(g_cap);
+  t.f.dt = (float)tp->dt_s;
+  t.f.nu_dt = (float)(nu_max * tp->dt_s);
+  t.f.xbin = (float)xbin;
+  t.f.inv_xbin = (float)(1.0 / xbin);
+  t.f.s_max = (float)(src->e_cut_ev / (src->e_cut_ev + src->u_s_ev));
+  t.f.u_s = (float)src->u_s_ev;
+  t.f.v_per_sqrt_ev = (float)std::sqrt(2.0 * kE / m);
+  t.f.e_half_m = (float)(0.5 * m / kE);
+  t.f.ebin = (float)tp->ebin_ev;
+  t.f.tbin = (float)tp->tbin_s;
+  t.dt = tp->dt_s;
   t.n_ebins = tp->n_ebins;
   t.n_tbins = tp->n_tbins;
   t.n_xbins = tp->mode == PM_TP_NORMAL ? tp->n_xbins : 0;
-  t.xbin = tp->gap_m / std::max(tp->n_xbins, 1);
-  t.inv_xbin = 1.0 / t.xbin;
   t.mode = tp->mode;
   t.scatter = tp->scatter;
   t.electrode = src->electrode;
-  t.dt = tp->dt_s;
-  t.nu_dt = t.nu_max * tp->dt_s;
   t.e_max = tp->e_max;
   t.n_atoms = src->n_atoms;
   t.first_atom = src->first_atom;
   t.seed = src->seed;
   t.job = src->job_id;
-  t.f.L = (float)t.L;
-  t.f.inv_L = (float)(1.0 / t.L);
-  t.f.inv_nu = (float)t.inv_nu_max;
-  t.f.sig_gas = (float)t.sig_gas;
-  t.f.m_ratio = (float)t.m_ratio;
-  t.f.M_ratio = (float)t.M_ratio;
-  t.f.sg_exp = (float)t.sg_exp;
-  t.f.log2_gcap = (float)t.log2_gcap;
-  t.f.dt = (float)t.dt;
-  t.f.nu_dt = (float)t.nu_dt;
-  t.f.xbin = (float)t.xbin;
-  t.f.inv_xbin = (float)t.inv_xbin;
-  t.f.s_max = (float)t.s_max;
-  t.f.u_s = (float)t.u_s;
-  t.f.v_per_sqrt_ev = (float)t.v_per_sqrt_ev;
-  t.f.e_half_m = (float)t.e_half_m;
-  t.f.ebin = (float)t.ebin;
-  t.f.tbin = (float)t.tbin;
   const TpLayout L = tp_layout(tp);
   pm::TpTally* tal = reinterpret_cast<pm::TpTally*>(base + L.tally);
   uint64_t* eh = reinterpret_cast<uint64_t*>(base + L.e_hist);
@@ -893,7 +877,7 @@ pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, ch
   const int nx = t.n_xbins;
   if (nx) {
     const double per_atom = src->flux_m2s / (double)std::max<int64_t>(src->n_atoms, 1);
-    PM_TRY(pm::launch_tp_profiles(prof, nx, t.xbin, per_atom, pout, st));
+    PM_TRY(pm::launch_tp_profiles(prof, nx, xbin, per_atom, pout, st));
   }
   // The results come back in one copy where there is a host buffer for them (40 KB
   // with the usual bins; a flight of 10k atoms 254 -> 144 us), else one by one: each
@@ -929,7 +913,7 @@ pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, ch
   out->e_sum_target = (double)(int64_t)h.sum[0] / 1048576.0;
   out->eta = src->n_atoms > 0 ? (double)h.n_sub / (double)src->n_atoms : 0.0;
   out->deposition_flux = out->eta * src->flux_m2s;
-  out->nu_max = t.nu_max;
+  out->nu_max = nu_max;
   // the three counts are taken apart from one another: each atom ends exactly once
   return out->n_substrate + out->n_target + out->n_unfinished == src->n_atoms ? PM_OK : PM_EDEVICE;
 }

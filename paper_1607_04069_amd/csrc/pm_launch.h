@@ -49,31 +49,29 @@ hipError_t launch_diag_reset(const CaseConst&, const GridPtrs&, Ctrl*, hipStream
 
 // The flight's constants in its own precision (in registers, not converted there).
 struct TpFloat {
-  float L, inv_L, inv_nu, sig_gas, m_ratio, M_ratio, sg_exp, log2_gcap, dt, nu_dt, xbin, inv_xbin, s_max, u_s,
-      v_per_sqrt_ev, e_half_m, ebin, tbin;
+  float L, inv_L;
+  float inv_nu;              // 1 / n_gas (sigma g)_max (infinity without gas)
+  float sig_gas;             // sqrt(k_B T / m_gas)
+  float m_ratio, M_ratio;    // m/(m+M), M/(m+M)
+  float sg_exp;              // 2 - 2 omega: (sigma g) ~ g^sg_exp for VHS
+  float log2_gcap;           // log2 of the majorant's relative speed
+  float dt;                  // fixed flight time (0: gridless, from the majorant)
+  float nu_dt;               // n_gas (sigma g)_max dt: the fixed-step probability at the majorant
+  float xbin, inv_xbin;      // cell width and its inverse, m
+  float s_max, u_s;          // Thompson inversion
+  float v_per_sqrt_ev;       // sqrt(2 e / m_test)
+  float e_half_m;            // 0.5 m / e: eV per (m/s)^2
+  float ebin, tbin;
 };
 
 struct TpConst {
   TpFloat f;
-  double L, lat;
-  double nu_max;             // n_gas (sigma g)_max
-  double inv_nu_max;
-  double sg_exp;             // 2 - 2 omega: (sigma g) ~ g^sg_exp for VHS
-  double log2_gcap;          // log2 of the majorant's relative speed
-  double sig_gas;            // sqrt(k_B T / m_gas)
-  double m_ratio, M_ratio;   // m/(m+M), M/(m+M)
-  double s_max, u_s;         // Thompson inversion
-  double v_per_sqrt_ev;      // sqrt(2 e / m_test)
-  double e_half_m;           // 0.5 m / e: eV per (m/s)^2
-  double ebin, tbin;
+  double dt;                 // for a fixed step's clock, its steps times dt
   int n_ebins, n_tbins;
   int n_xbins;               // cells of the track-length profiles (0: none)
-  double xbin, inv_xbin;     // cell width and its inverse, m
   int mode;
   int scatter;               // 0 VHS isotropic, 1 M1
   int electrode;             // emission from the target (0) or the substrate (1)
-  double dt;                 // fixed flight time (0: gridless, from the majorant)
-  double nu_dt;              // nu_max dt: the fixed-step probability at the majorant
   int64_t e_max;
   int64_t n_atoms, first_atom;
   uint64_t seed, job;
