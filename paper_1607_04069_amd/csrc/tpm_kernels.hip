@@ -855,14 +855,19 @@ static int compute_units() {
 // than the six to eight that fit (1e6 atoms at 5 Pa: 9.3 ms, 10.3 with six, 9.8
 // with two; 1e7 at 0.5 Pa 1.27 against 1.26 and 1.55).  An atom starts with more
 // lanes than one as long as its launch stays within as many wavefronts (a fixed
-// step, whose lanes all count, twice as many: 1e5 atoms 7.9 ms against 9.3).
+// step, whose lanes all count, twice as many: 1e5 atoms 7.9 ms against 9.3), and as
+// long as a fixed step's event limit gives each lane eight events: more workgroups
+// have more tallies to add (10 steps of 10007 atoms 141 us with 64 lanes an atom, 60
+// with one; 60 steps of 50021 in the periodic box 161 us with 16, 130 with four).
 hipError_t launch_tp_flight(TpConst T, TpTally* tally, uint64_t* e_hist, uint64_t* th_hist, uint64_t* tof_hist,
                             TpTrace trace, int64_t* prof, hipStream_t st) {
   const int64_t most = (int64_t)compute_units() * 4 * 4;
   const bool fixed = T.dt > 0.0;
   const int widest = fixed ? kWidest<true> : kWidest<false>;
   T.wlog = 0;
-  while (T.wlog < widest && T.n_atoms <= (fixed ? 128 : 64) * most >> (T.wlog + 1)) ++T.wlog;
+  while (T.wlog < widest && T.n_atoms <= (fixed ? 128 : 64) * most >> (T.wlog + 1) &&
+         (!fixed || (int64_t)8 << (T.wlog + 1) <= T.e_max))
+    ++T.wlog;
   const int64_t per_wave = 64 >> T.wlog;
   const int64_t waves = std::min((T.n_atoms + per_wave - 1) / per_wave, most);
   const int grid = (int)std::max<int64_t>(1, (waves + kBlock / 64 - 1) / (kBlock / 64));

@@ -1,0 +1,22 @@
+"""Fixed-step flights with a low event limit take few lanes an atom (runs on an MI355X):
+at the limits where the number of lanes changes an atom's flight is that of a launch
+with one lane per atom."""
+import numpy as np
+import pytest
+
+from test_gpu_tpm_lanes import N_ONE_LANE, _inputs, pm  # noqa: F401  (the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("e_max", [1, 8, 15, 16, 64, 127, 512])
+def test_event_limits_do_not_change_an_atom(pm, e_max, mode):
+    kw = dict(p_pa=5.0, mode=mode, dt_s=1e-7, e_max=e_max, scatter=mode)
+    big = pm.run_test_particles(*_inputs(N_ONE_LANE, **kw), trace=True)["trace"]
+    for n, first in ((1, 5), (63, 100), (4097, 1000), (66_000, 30_001)):
+        small = pm.run_test_particles(*_inputs(n, first, **kw), trace=True)
+        for k, v in small["trace"].items():
+            assert np.array_equal(v, big[k][first:first + n], equal_nan=v.dtype.kind == "f"), (n, k)
+        assert small["events"] == int(small["trace"]["events"].astype(np.int64).sum())
+        assert small["n_unfinished"] == int((small["trace"]["wall"] == 2).sum())
