@@ -841,6 +841,12 @@ pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, ch
   t.f.e_half_m = (float)(0.5 * m / kE);
   t.f.ebin = (float)tp->ebin_ev;
   t.f.tbin = (float)tp->tbin_s;
+  // what an atom at the surface binding energy meets on a straight way across the gap,
+  // or on the random walk that many collisions make of it (sputtered Al in argon over
+  // 40 mm: 5.7 at 0.5 Pa and 450 at 5 Pa, where 4.3 and 440 are met)
+  const double across = tp->gap_m / (std::sqrt(2.0 * kE / m) * std::sqrt(src->u_s_ev)), k = nu_max * across;
+  const double events = tp->mode == PM_TP_BOX ? (double)tp->e_max : tp->dt_s > 0 ? across / tp->dt_s : k + 2.5 * k * k;
+  t.expect = (float)std::min(events, (double)tp->e_max);
   t.dt = tp->dt_s;
   t.n_ebins = tp->n_ebins;
   t.n_tbins = tp->n_tbins;

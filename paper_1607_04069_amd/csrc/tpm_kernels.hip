@@ -537,10 +537,10 @@ __global__ __launch_bounds__(kBlock, 6) void k_tp_flight(TpConst T, TpTally* tal
       if (q.dry) break;
       continue;
     }
-    if (q.dry && wlog < kWidest<kFixed> && 2 * n * W <= 64) {
+    if (q.dry && wlog < T.widest && 2 * n * W <= 64) {
       // no atoms are left to take: move the groups together and widen them
       int to = wlog + 1;
-      while (to < kWidest<kFixed> && (n << (to + 1)) <= 64) ++to;
+      while (to < T.widest && (n << (to + 1)) <= 64) ++to;
       const bool lead = alive && i == 0;
       // leaders send their lane to the lane of their rank (at most 31), others to lane 63
       const int of = __builtin_amdgcn_ds_permute((lead ? lanes_below(live, lane) : 63) << 2, lane);
@@ -855,25 +855,34 @@ static int compute_units() {
 // than the six to eight that fit (1e6 atoms at 5 Pa: 9.3 ms, 10.3 with six, 9.8
 // with two; 1e7 at 0.5 Pa 1.27 against 1.26 and 1.55).  An atom starts with more
 // lanes than one as long as its launch stays within as many wavefronts (a fixed
-// step, whose lanes all count, twice as many: 1e5 atoms 7.9 ms against 9.3), and as
-// long as a fixed step's event limit gives each lane eight events: more workgroups
-// have more tallies to add (10 steps of 10007 atoms 141 us with 64 lanes an atom, 60
-// with one; 60 steps of 50021 in the periodic box 161 us with 16, 130 with four).
+// step, whose lanes all count, twice as many: 1e5 atoms 7.9 ms against 9.3), but with
+// one lane if it meets less than one event on its way (1e4 atoms at 0.1 Pa 120 -> 72
+// us), and no more lanes than leave each eight events up to the event limit: more
+// workgroups have more tallies to add (10 steps of 10007 atoms 141 us with 64 lanes an
+// atom, 60 with one; 60 steps of 50021 in the periodic box 161 us with 16, 130 with
+// four).  A fixed step at which many tests succeed has little to look ahead for: its
+// lanes stay below 16 over the probability at the majorant (at 1.6, 10247 atoms 4.1 ms
+// with 64 lanes and 2.6 with 8; at 0.16 5.5 with 64 and 6.1 with 32).
 hipError_t launch_tp_flight(TpConst T, TpTally* tally, uint64_t* e_hist, uint64_t* th_hist, uint64_t* tof_hist,
                             TpTrace trace, int64_t* prof, hipStream_t st) {
   const int64_t most = (int64_t)compute_units() * 4 * 4;
   const bool fixed = T.dt > 0.0;
-  const int widest = fixed ? kWidest<true> : kWidest<false>;
+  T.widest = fixed ? kWidest<true> : kWidest<false>;
+  while (T.widest > 1 && T.f.nu_dt * (float)(1 << T.widest) > 16.0f) --T.widest;
   T.wlog = 0;
-  while (T.wlog < widest && T.n_atoms <= (fixed ? 128 : 64) * most >> (T.wlog + 1) &&
-         (!fixed || (int64_t)8 << (T.wlog + 1) <= T.e_max))
-    ++T.wlog;
+  if (T.expect >= 1.0f)
+    while (T.wlog < T.widest && T.n_atoms <= (fixed ? 128 : 64) * most >> (T.wlog + 1) &&
+           (int64_t)8 << (T.wlog + 1) <= T.e_max)
+      ++T.wlog;
   const int64_t per_wave = 64 >> T.wlog;
   const int64_t waves = std::min((T.n_atoms + per_wave - 1) / per_wave, most);
   const int grid = (int)std::max<int64_t>(1, (waves + kBlock / 64 - 1) / (kBlock / 64));
-  // eight runs per wavefront: the atomics on the queue stay rare and the runs of
-  // the last ones short
-  T.run = std::max(per_wave, std::min<int64_t>(T.n_atoms / (waves * 8), 512));
+  // eight runs per wavefront: the atomics on the queue stay rare and the runs of the
+  // last ones short; two where the atoms end so soon that the atomics would take
+  // turns (3e6 atoms without gas 480 -> 190 us, 1e6 at 0.5 Pa 390 -> 320; at 1 Pa, 16
+  // events an atom, 640 either way; at 30 events 310 with eight and 340 with two)
+  const int64_t runs = T.expect < 16.0f ? 2 : 8;
+  T.run = std::max(per_wave, std::min<int64_t>(T.n_atoms / (waves * runs), 512));
   T.first_run = (int64_t)grid * (kBlock / 64) * T.run;
   const size_t lds = (size_t)(T.n_ebins + kTpThetaBins + T.n_tbins) * 4 +
                      (T.n_xbins ? (size_t)4 * (T.n_xbins + 1) * 8 : 0);
