@@ -460,11 +460,11 @@ void pm_destroy_case(pm_case* c);
  * A parameter sweep (the discharge of Sec. III and IV.A at several pressures,
  * voltages and grid sizes, across the collisional regimes of Sec. II) is a set
  * of cases that never interact.  A batch advances all of them together:
- * each time step of every case in the batch is one launch of the push and one
- * of the collision kernel (per lane, below), the workgroups of case 0 first,
- * then those of case 1, and so on, each case receiving a share of one resident
- * wave of workgroups in proportion to its particles.  Every case computes exactly what pm_step computes for it
- * alone: its random numbers depend only on (seed, case_id, particle id, step),
+ * each time step of every case in the batch is one launch (per lane, below), or
+ * for a single step one of the push and one of the collision kernel, each case
+ * receiving a share of one resident wave of workgroups in proportion to its
+ * particles or, in the one launch, its work.  Every case computes exactly what
+ * pm_step computes for it alone: its random numbers depend only on (seed, case_id, particle id, step),
  * and its charge sums are integers, so the state of each case, compared
  * particle by particle by id, is bit-identical alone and in a batch.
  *

@@ -1289,17 +1289,17 @@ pm_status pm_run_test_particles_static(const pm_tp_params* tp, const pm_tp_sourc
 }  // extern "C"
 
 // ------------------------------------------------------------------ batches
-// Many independent cases (a parameter sweep) advanced by the same launches, one
-// push and one collision launch per time step and lane.  The working workgroups of every case come first in the grid, case by
-// case, so the serial part of a case (its field solve) overlaps the particle
-// work of the cases after it; the workgroups that hold slots only when a case
-// outgrows its share follow.  Device tables in a caller-provided arena:
-//   [KArgs of each case][step, collision and sort workgroups per case]
-//   [step, collision and sort work lists],  work entry = case << 16 | local
+// Many independent cases (a parameter sweep) advanced by the same launches, per time
+// step and lane one fused launch, or for a single step one push and one collision
+// launch.  A launch's workgroups are those of all its cases, the ones with the most
+// tiles first; in the push, the workgroups that hold slots only when a case outgrows
+// its share follow.  Device tables in a caller-provided arena:
+//   [KArgs of each case][step, collision, sort and fused workgroups per case]
+//   [step, collision, sort and fused work lists],  work entry = case << 16 | local
 //   workgroup, with room for the largest step grid of every case.
-// The cases of a batch may run in up to four lanes, each on its own stream:
-// while one lane's collision kernel (latency-bound) runs, another lane's push
-// kernel (bandwidth-bound) fills the GPU.  A lane's work lists are a segment of
+// The cases of a batch may run in up to four lanes, each on its own stream: one
+// lane's workgroups that wait (for the field, the collisions' records, the last of
+// their launch) leave the GPU to another's that stream.  A lane's work lists are a segment of
 // the batch's lists.
 struct BatchLane {
   int step_off, step_n, mcc_off, mcc_n, sort_off, sort_n, fused_off, fused_n, maxN;
@@ -1394,8 +1394,6 @@ pm_status batch_layout(pm_case* const* cases, int32_t n, BatchLayout* L) {
   return PM_OK;
 }
 
-// Share the working workgroups out in proportion to the cases' initial
-// particles and write the tables for the batch's shape.  Synchronises.
 // Share total workgroups among the cases of one lane in proportion to weight,
 // each share rounded up from (total - n), so that they sum to at most total
 // and no case gets less than its part; each share at least 1 and at most cap[i].
@@ -1412,12 +1410,6 @@ std::vector<int64_t> shares(const std::vector<double>& weight, int64_t total, co
   return out;
 }
 
-// Write the batch's tables for its shape and members.  An unslotted batch
-// shares one resident wave of push workgroups among all its cases in
-// proportion to their initial particles and groups the cases into lanes by
-// size; a slotted batch puts slot i in lane i mod lanes, gives each lane a
-// fixed part of each kernel's resident wave and pads its lists with idle
-// entries.  Synchronises hip_stream.
 // Tiles t in [lo, hi) with t = q (mod m): the share of workgroup q of m in a
 // strided walk over tiles lo..hi-1.
 int64_t strided_count(int64_t lo, int64_t hi, int64_t q, int64_t m) {
@@ -1426,6 +1418,13 @@ int64_t strided_count(int64_t lo, int64_t hi, int64_t q, int64_t m) {
   return first < hi ? (hi - 1 - first) / m + 1 : 0;
 }
 
+// Write the batch's tables for its shape and members.  An unslotted batch
+// shares one resident wave of push workgroups among all its cases in
+// proportion to their initial particles and groups the cases into lanes by
+// size; a slotted batch puts slot i in lane i mod lanes, gives each lane a
+// fixed part of each kernel's resident wave and pads its lists with idle
+// entries.  The workgroups of fused steps are shared out likewise, by the cases'
+// work.  Synchronises hip_stream.
 template <typename R>
 pm_status write_tables(pm_batch* b, hipStream_t st) {
   const int n = (int)b->cases.size();

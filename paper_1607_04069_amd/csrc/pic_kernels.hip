@@ -1,6 +1,6 @@
 // PIC/MCC kernels for gfx950 (Sec. IV.A, Fig. 4 of arXiv:1607.04069).
 //
-// One time step is two launches.  k_step (the push) stages the field of step l
+// A single time step is two launches.  k_step (the push) stages the field of step l
 // in LDS and advances the cell-sorted particles of its tiles: gather, leapfrog
 // push of Eqs. (3)-(4), wall absorption, and the deposit of the new positions
 // into an LDS tile of the next step's charge (linear weighting, integer units of
@@ -9,10 +9,11 @@
 // candidate list instead of being touched further.  k_mcc (the collisions) walks
 // the candidate lists: selection of Eq. (6), kinematics, births, the next
 // waiting time; its last workgroup to finish solves Poisson's equation for step
-// l+1, accumulates the diagnostics and publishes the step counter.  Every K
-// steps a counting sort by cell compacts the slots.  An RF cycle is the chain of
-// these launches captured in a HIP graph; the _batch forms run many independent
-// cases in the same launches from per-case work lists.
+// l+1, accumulates the diagnostics and publishes the step counter.  Several steps
+// of one call take one launch each, k_fused, and leave the same state through
+// k_commit.  Every K steps a counting sort by cell compacts the slots.  An RF cycle
+// is the chain of these launches captured in a HIP graph; the _batch forms run many
+// independent cases in the same launches from per-case work lists.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -555,7 +556,7 @@ __global__ __launch_bounds__(kBlock) void k_field(KArgs<R> A, int want_phi) {
 }
 
 // ------------------------------------------------------------------ the step
-// One time step is two launches.  The push kernel (k_step) gathers, pushes,
+// A single time step is two launches.  The push kernel (k_step) gathers, pushes,
 // applies the walls and deposits every particle of its range, and lists the
 // null-collision candidates; the collision kernel (k_mcc) runs the candidates
 // (Eq. (6) and the selection rule), deposits the births, and its last workgroup
@@ -706,15 +707,9 @@ __device__ __forceinline__ void deposit_global(int64_t* Qs, uint32_t* cell_count
   if (cell_count) atomicAdd(&cell_count[j], 1u);
 }
 
-// Null-collision Monte Carlo collision of a candidate at step l (Eq. (6) and
-// the selection rule of Sec. IV.A).  xn is x^(l+1) and un v_x^(l+1/2) in cell
-// units, both as the push left them.  Qn: the charge buffer of step l+1.  One
-// Philox draw gives all of the candidate's uniforms: U0 selects the process,
-// U1-U2 (and U3-U4 for ionisation) the electron directions or U1-U4 the ion's
-// Maxwellian partner, U7 the waiting time to its next candidate.  An entry
-// marked redraw is an examination at a cut wait: it takes only the fresh wait.
 // The electron and the ion of an ionisation at x = xn: the electron's velocity
-// (ex, ey, ez) in m/s, the ion's Maxwellian at the gas temperature.
+// (ex, ey, ez) in m/s, the ion's Maxwellian at the gas temperature.  They take slots
+// base_e + alloc[0]++ and base_i + alloc[1]++ and add their charge to Qn.
 template <typename R>
 __device__ __forceinline__ void mcc_births(const KArgs<R>& A, uint32_t buf, int64_t l, R xn, R ex, R ey, R ez, uint64_t id,
                                         int64_t* Qn, uint32_t* cell_count, uint32_t* cnt, unsigned long long* alloc,
@@ -748,8 +743,14 @@ __device__ __forceinline__ void mcc_births(const KArgs<R>& A, uint32_t buf, int6
   }
 }
 
-// U: its draw (collision_draw).  A birth takes slots base_e + alloc[0]++ and
-// base_i + alloc[1]++.
+// Null-collision Monte Carlo collision of a candidate at step l (Eq. (6) and
+// the selection rule of Sec. IV.A).  xn is x^(l+1) and un v_x^(l+1/2) in cell
+// units, both as the push left them.  Qn: the charge buffer of step l+1.  One
+// Philox draw U (collision_draw) gives all of the candidate's uniforms: U0 selects
+// the process, U1-U2 (and U3-U4 for ionisation) the electron directions or U1-U4 the
+// ion's Maxwellian partner, U7 the waiting time to its next candidate.  An entry
+// marked redraw is an examination at a cut wait: it takes only the fresh wait.
+// Births take slots as mcc_births says.
 template <typename R>
 __device__ __forceinline__ void mcc_candidate(const KArgs<R>& A, int s, int64_t k, bool redraw, uint32_t buf,
                                               int64_t l, R xn, R un, R uy, R uz, uint64_t id, const Uniforms8<R>& U,

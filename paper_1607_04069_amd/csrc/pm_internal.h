@@ -39,9 +39,10 @@ struct FusedNext {
   int pb;                    // phase bin (-1: none)
 };
 
-// Device-resident control block of one case.  Written by the last collision
-// workgroup of each step (the step epilogue) and read by every workgroup of the
-// next step.
+// Device-resident control block of one case, read by every workgroup of a step.
+// Written by the last collision workgroup of a two-launch step (the step epilogue),
+// and by the commit after a run of one-launch steps, which keep their own state in
+// the last fields.
 struct Ctrl {
   int64_t step;              // index l of the next step to run
   int64_t n_range[2];        // slots [0, n_range) are scanned this step
@@ -67,9 +68,10 @@ struct Ctrl {
   uint32_t circ_ready;       // sigma_init recorded
   uint32_t pad32;
   uint64_t pad[3];
-  // Fused steps only (k_fused; all zero between a commit and the next of them,
-  // but range and net_sum): of launch i, at index i mod 3, its births, the net
+  // Fused steps only (k_fused): of launch i, at index i mod 3, its births, the net
   // charge absorbed at electrode 0, and its slot ranges and the net charge before it.
+  // Between a commit and the next of them born and net are zero; the others hold what
+  // the last launches left, which launch 0 does not read.
   uint64_t born[3][2];
   int64_t net[3];
   int64_t range[3][2];
