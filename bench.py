@@ -12,8 +12,9 @@ case runs 200 RF cycles (--case-cycles): by default 2 warm-up cycles and the
 other 198 timed, so the rate covers the whole run as the discharges settle (their
 live particles fall to about half); with fewer timed steps, untimed cycles
 before the warm-up make the timed ones the last of the 200.
-The push and collision kernels are first timed alone (single steps, HIP events)
-from the seeded initial load, for the roofline.
+First, from the seeded initial load, the push and collision kernels of single steps
+are timed alone (HIP events), then the one-launch step that the RF cycles run, for the
+roofline.
 
 Beside it, measured after the timed region: the same 64 cases stepped one case
 at a time (each from its own RF-cycle graph), the plain single working-size
@@ -34,6 +35,7 @@ sys.path.insert(0, ROOT)
 METRIC = "particle-steps/s (batched vs plain) at oracle-matched stats; p50/p99 case latency"
 HBM_PEAK_GBS = 8000.0
 PROBE = 100
+STEP_RUN = 50
 
 
 def parse():
@@ -54,11 +56,12 @@ def parse():
                     help="run only the served stream (after the batched sweep that sets its capacity)")
     ap.add_argument("--copy-probe-mb", type=int, default=0,
                     help="after the run, copy a buffer of this many MiB (counter calibration)")
-    ap.add_argument("--probe", choices=("push", "flight"), default=None,
-                    help="for counter passes: only the push/collision probe (single batch steps) or only "
-                         "the atom flights, with plain launches and no graph; prints one JSON line")
+    ap.add_argument("--probe", choices=("push", "step", "flight"), default=None,
+                    help="for counter passes: only the push/collision probe (single batch steps), only the "
+                         "one-launch steps or only the atom flights, with plain launches and no graph; "
+                         "prints one JSON line")
     ap.add_argument("--sweep-cases", type=int, default=64,
-                    help="cases of the push probe's sweep (128: twice the working set, the 64-case "
+                    help="cases of the push and step probes' sweep (128: twice the working set, the 64-case "
                          "shape with its workgroups doubled)")
     return ap.parse_args()
 
@@ -76,6 +79,29 @@ def kernel_probe(batch, cases, n):
     ps = sum(y["particle_steps"] - x["particle_steps"] for x, y in zip(d0, d1))
     cand = sum(int(sum(y["candidates"]) - sum(x["candidates"])) for x, y in zip(d0, d1))
     return push_ms, mcc_ms, ps / n, cand / n
+
+
+def step_probe(batch, cases, torch):
+    """Average duration of a launch of the one-launch step (k_fused_batch) over two runs
+    of STEP_RUN steps, each right after a sort, one lane: HIP events around the run, so
+    that the gaps between launches (about a microsecond each) and one commit a run are
+    in it; and the particle-steps per launch."""
+    shape = batch.launch_shape()
+    ms = ps = 0.0
+    for _ in range(2):
+        batch.set_launch_shape(lanes=1, sort_interval=1)
+        batch.step(1)
+        batch.set_launch_shape(lanes=1, sort_interval=0)
+        n0 = sum(c.sample_diagnostics()["particle_steps"] for c in cases)
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        batch.step(STEP_RUN)
+        b.record()
+        b.synchronize()
+        ms += a.elapsed_time(b)
+        ps += sum(c.sample_diagnostics()["particle_steps"] for c in cases) - n0
+    batch.set_launch_shape(**shape)
+    return ms / (2 * STEP_RUN), ps / (2 * STEP_RUN)
 
 
 def flight_probe(pm, W, torch):
@@ -107,11 +133,11 @@ def copy_probe(mb, torch):
     print(json.dumps({"copy_probe_bytes_read": 4 * n, "copy_probe_bytes_written": 4 * n}), flush=True)
 
 
-def measured_traffic(probe_launches):
-    """HBM bytes per probe launch of the batched step kernel from the committed
-    counter passes (FETCH_SIZE and WRITE_SIZE, each scaled by the same counter's
-    reading for a copy of known size), or None when the kernel source changed."""
-    path = os.path.join(ROOT, "profiles", "k_step_batch_traffic.json")
+def measured_traffic():
+    """HBM bytes per launch of the step probe's kernel from the committed counter
+    passes (FETCH_SIZE and WRITE_SIZE, each scaled by the same counter's reading for
+    a copy of known size), or None when the kernel source changed."""
+    path = os.path.join(ROOT, "profiles", "k_fused_batch_traffic.json")
     src = os.path.join(ROOT, "paper_1607_04069_amd", "csrc", "pic_kernels.hip")
     try:
         with open(path) as f:
@@ -120,7 +146,7 @@ def measured_traffic(probe_launches):
             digest = hashlib.sha256(f.read()).hexdigest()
     except OSError:
         return None
-    if t.get("source_sha256") != digest or t.get("probe_launches") != probe_launches:
+    if t.get("source_sha256") != digest or t.get("probe_launches") != 2 * STEP_RUN:
         return None
     return t["bytes_per_launch"]
 
@@ -254,33 +280,48 @@ def main():
     for c in cases:
         c.sample_diagnostics(reset=True)
 
-    # The dominant kernel, the push, timed first from the seeded initial load (the
-    # same launches in every run, so the counter passes of this command see them
-    # too): per particle-step it must move x and v_x in and out in FP32 (16 B).
-    # The collision kernel must move, per null-collision candidate, its list entry
-    # in (slot, x and v_x: 12 B), its record in (v_y, v_z, id: 16 B) and its next
-    # examination code out (2 B): 30 B.
-    progress(f"kernel probe: {args.kernel_probe} single steps of {len(cases)} cases")
-    k_ms, mcc_ms, ps_per_launch, cand_per_launch = kernel_probe(batch, cases, args.kernel_probe)
-    if args.probe == "push":
-        alg = 16.0 * ps_per_launch
-        print(json.dumps({"probe": "push", "cases": n_sweep, "launch_shape": shape, "shape_source": source,
-                          "probe_launches": args.kernel_probe, "push_ms": k_ms, "mcc_ms": mcc_ms,
-                          "particle_steps_per_launch": ps_per_launch, "candidates_per_launch": cand_per_launch,
-                          "push_alg_bytes_per_launch": alg, "push_alg_gbs": alg / (k_ms * 1e-3) / 1e9,
-                          "push_frac": alg / (k_ms * 1e-3) / 1e9 / HBM_PEAK_GBS}), flush=True)
+    # The kernels timed from the seeded initial load (the same launches in every run,
+    # so the counter passes of this command see them too).  Per particle-step the push
+    # must move x and v_x in and out in FP32 (16 B), and so must the one-launch step,
+    # the dominant kernel of the RF cycles.  The collision kernel of a single step must
+    # move, per null-collision candidate, its list entry in (slot, x and v_x: 12 B), its
+    # record in (v_y, v_z, id: 16 B) and its next examination code out (2 B): 30 B.
+    if args.probe == "step":
+        ms, ps_per_step = step_probe(batch, cases, torch)
+        alg = 16.0 * ps_per_step
+        print(json.dumps({"probe": "step", "cases": n_sweep, "probe_launches": 2 * STEP_RUN, "step_ms": ms,
+                          "particle_steps_per_launch": ps_per_step, "step_alg_bytes_per_launch": alg,
+                          "step_alg_gbs": alg / (ms * 1e-3) / 1e9,
+                          "step_frac": alg / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS}), flush=True)
         batch.close()
         for c in cases:
             c.close()
         if args.copy_probe_mb:
             copy_probe(args.copy_probe_mb, torch)
         return
+    progress(f"kernel probe: {args.kernel_probe} single steps of {len(cases)} cases")
+    push_ms, mcc_ms, ps_per_push, cand_per_launch = kernel_probe(batch, cases, args.kernel_probe)
+    if args.probe == "push":
+        alg = 16.0 * ps_per_push
+        print(json.dumps({"probe": "push", "cases": n_sweep, "launch_shape": shape, "shape_source": source,
+                          "probe_launches": args.kernel_probe, "push_ms": push_ms, "mcc_ms": mcc_ms,
+                          "particle_steps_per_launch": ps_per_push, "candidates_per_launch": cand_per_launch,
+                          "push_alg_bytes_per_launch": alg, "push_alg_gbs": alg / (push_ms * 1e-3) / 1e9,
+                          "push_frac": alg / (push_ms * 1e-3) / 1e9 / HBM_PEAK_GBS}), flush=True)
+        batch.close()
+        for c in cases:
+            c.close()
+        if args.copy_probe_mb:
+            copy_probe(args.copy_probe_mb, torch)
+        return
+    step_ms, ps_per_launch = step_probe(batch, cases, torch)
     alg_bytes = 16.0 * ps_per_launch
-    achieved = alg_bytes / (k_ms * 1e-3) / 1e9
-    traffic = measured_traffic(args.kernel_probe)
+    achieved = alg_bytes / (step_ms * 1e-3) / 1e9
+    traffic = measured_traffic()
 
     settle = max(0, args.case_cycles - args.warmup - args.steps)
-    progress(f"push {k_ms * 1e3:.1f} us, collisions {mcc_ms * 1e3:.1f} us; settling {settle} RF cycles")
+    progress(f"one-launch step {step_ms * 1e3:.1f} us (push {push_ms * 1e3:.1f} us, collisions {mcc_ms * 1e3:.1f} us "
+             f"in a single step); settling {settle} RF cycles")
     t_settle = time.perf_counter()
     batch.step_rf_cycles(settle)
     torch.cuda.synchronize()
@@ -318,7 +359,7 @@ def main():
         one.step_rf_cycles(1)
         n1, d1 = timed_cycles(one, [one], 3, torch)
         side["single_case_particle_steps_per_s"] = n1 / d1
-        side["single_case_push_ms"], side["single_case_collision_ms"] = one.time_kernels(50)
+        side["single_case_single_step_push_ms"], side["single_case_single_step_collision_ms"] = one.time_kernels(50)
         side["single_case_shape"] = one.launch_shape()
         shape1 = one.launch_shape()
         one.close()
@@ -333,7 +374,7 @@ def main():
         side["paper_drive_particle_steps_per_s"] = n1 / d1
         one.close()
         # the working case with 32 phase bins and the flux profiles sampled every
-        # step (the extra read of x and v_x by k_flux)
+        # step (inside the step's kernel)
         one = pm.Case(dict(pw, n_phase=32, flux_profiles=1))
         one.set_launch_shape(**shape1)
         one.step_rf_cycles(1)
@@ -362,20 +403,19 @@ def main():
         if args.serve_requests:
             progress(f"served stream: {args.serve_requests} requests")
             side["serving"] = serving_leg(pm, W, args, value)
-        # the same push probe on twice the sweep (its first 64 cases and 64 more
+        # the same step probe on twice the sweep (its first 64 cases and 64 more
         # from the same distribution, 3.5e7 particle-steps per launch: particle
         # streams well above the 256 MB Infinity Cache), in the 64-case shape
         # with its workgroups doubled
-        progress("push probe on 128 sweep cases")
+        progress("step probe on 128 sweep cases")
         p128 = W.sweep_cases(128)
         c128 = [pm.Case(p) for p in p128]
         b128 = pm.Batch(c128)
         b128.set_launch_shape(**dict(shape, work_groups=shape["work_groups"] * 2))
-        k2, m2, ps2, cand2 = kernel_probe(b128, c128, args.kernel_probe)
+        k2, ps2 = step_probe(b128, c128, torch)
         probe128 = {"cases": 128, "kernel_ms": k2, "particle_steps_per_launch": ps2,
                     "alg_bytes_per_launch": 16.0 * ps2, "achieved": 16.0 * ps2 / (k2 * 1e-3) / 1e9,
-                    "frac": 16.0 * ps2 / (k2 * 1e-3) / 1e9 / HBM_PEAK_GBS, "collision_kernel_ms": m2,
-                    "candidates_per_launch": cand2}
+                    "frac": 16.0 * ps2 / (k2 * 1e-3) / 1e9 / HBM_PEAK_GBS}
         b128.close()
         for c in c128:
             c.close()
@@ -402,16 +442,22 @@ def main():
                    "shape_source": source, **side},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "k_step_batch (push)", "kernel_ms": k_ms, "alg_bytes_per_launch": alg_bytes,
+                     "kernel": "k_fused_batch (one-launch step, one lane)", "kernel_ms": step_ms,
+                     "alg_bytes_per_launch": alg_bytes,
                      "design_bytes_per_particle_step": 18.0,
-                     "design_gbs": 18.0 * ps_per_launch / (k_ms * 1e-3) / 1e9,
+                     "design_gbs": 18.0 * ps_per_launch / (step_ms * 1e-3) / 1e9,
                      "particle_steps_per_launch": ps_per_launch,
+                     "timed_region_alg_gbs": 16.0 * value / 1e9,
                      "above_infinity_cache": probe128,
-                     "collision_kernel": {"kernel": "k_mcc_batch", "kernel_ms": mcc_ms,
-                                          "candidates_per_launch": cand_per_launch,
-                                          "alg_bytes_per_launch": 30.0 * cand_per_launch,
-                                          "achieved_gbs": 30.0 * cand_per_launch / (mcc_ms * 1e-3) / 1e9,
-                                          "bound": "hbm (gathered records share cache lines) and latency"}},
+                     "single_step": {"push": {"kernel": "k_step_batch", "kernel_ms": push_ms,
+                                              "alg_bytes_per_launch": 16.0 * ps_per_push,
+                                              "achieved_gbs": 16.0 * ps_per_push / (push_ms * 1e-3) / 1e9},
+                                     "collisions": {"kernel": "k_mcc_batch", "kernel_ms": mcc_ms,
+                                                    "candidates_per_launch": cand_per_launch,
+                                                    "alg_bytes_per_launch": 30.0 * cand_per_launch,
+                                                    "achieved_gbs": 30.0 * cand_per_launch / (mcc_ms * 1e-3) / 1e9,
+                                                    "bound": "hbm (gathered records share cache lines) and "
+                                                             "latency"}}},
     }
     if not args.no_cpu_baseline:
         progress("oracle on the host cores")
