@@ -261,7 +261,7 @@ def main():
         if args.copy_probe_mb:
             copy_probe(args.copy_probe_mb, torch)
         return
-    n_sweep = args.sweep_cases if args.probe == "push" else 64
+    n_sweep = args.sweep_cases if args.probe in ("push", "step") else 64
     params = W.sweep_cases(n_sweep)
     cases = [pm.Case(p) for p in params]
     batch = pm.Batch(cases)
