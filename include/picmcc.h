@@ -461,7 +461,8 @@ void pm_destroy_case(pm_case* c);
  * voltages and grid sizes, across the collisional regimes of Sec. II) is a set
  * of cases that never interact.  A batch advances all of them together:
  * each time step of every case in the batch is one launch (per lane, below), or
- * for a single step one of the push and one of the collision kernel, each case
+ * for a single step and for a very large batch one of the push and one of the
+ * collision kernel, each case
  * receiving a share of one resident wave of workgroups in proportion to its
  * particles or, in the one launch, its work.  Every case computes exactly what
  * pm_step computes for it alone: its random numbers depend only on (seed, case_id, particle id, step),

@@ -9,6 +9,7 @@
 #include <memory>
 #include <mutex>
 #include <new>
+#include <queue>
 #include <type_traits>
 #include <vector>
 
@@ -1410,6 +1411,37 @@ std::vector<int64_t> shares(const std::vector<double>& weight, int64_t total, co
   return out;
 }
 
+// The same for fused steps: one each, then one by one to the case whose workgroups
+// have most to do.  A launch lasts as long as its fullest workgroup, and with a few
+// workgroups a case the rounding above costs a quarter (one lane, us a step: 200
+// discharges of the sweep's distribution 447 -> 402, 64 96.7 -> 94.6; 256 of 20k + 20k
+// in FP64, 3 lanes, 156 -> 109).
+std::vector<int64_t> even_shares(const std::vector<double>& weight, int64_t total, const std::vector<int64_t>& cap) {
+  std::vector<int64_t> out(weight.size(), 1);
+  std::priority_queue<std::pair<double, size_t>> fullest;
+  for (size_t i = 0; i < weight.size(); ++i)
+    if (cap[i] > 1) fullest.push({weight[i], i});
+  for (int64_t left = total - (int64_t)weight.size(); left > 0 && !fullest.empty(); --left) {
+    const size_t i = fullest.top().second;
+    fullest.pop();
+    if (++out[i] < cap[i]) fullest.push({weight[i] / (double)out[i], i});
+  }
+  return out;
+}
+
+// Whether a batch's steps of one call are fused.  A batch of more particles than the
+// caches hold is streamed as fast by the push of two launches, at twice the
+// wavefronts, unless its collisions are what takes the time.  Two launches against
+// fused, us a step: FP32 (512 resident workgroups), 3 lanes, 0.5 to 3 Pa, 25M
+// particles 133 and 129, 33M 178 and 176, 54M 227 and 251, 56M at 50 Pa 562 and 480;
+// the sweep's distribution, 24M 146 and 133, 35M 194 and 198, 58M 306 and 334.  FP64
+// (256), 8M 103 and 91, 11M 125 and 120, 16M 147 and 155, 27M 223 and 245; 11M at 50
+// Pa 204 and 225.
+bool fuse_batch(bool fp64, double particles, double candidates, int64_t resident) {
+  if (fp64) return particles <= 40e3 * (double)resident;
+  return particles <= 65e3 * (double)resident || candidates > 0.08 * particles;
+}
+
 // Tiles t in [lo, hi) with t = q (mod m): the share of workgroup q of m in a
 // strided walk over tiles lo..hi-1.
 int64_t strided_count(int64_t lo, int64_t hi, int64_t q, int64_t m) {
@@ -1462,19 +1494,25 @@ pm_status write_tables(pm_batch* b, hipStream_t st) {
   // run side by side and one lane's workgroups can start as another's end (64
   // discharges in 3 lanes 99.9 -> 86.7 us a step, 16 in 2 lanes 28.0 -> 27.5, 8 in
   // 2 lanes 21.8 -> 16.8; in a single lane the second generation costs more than
-  // the balance gives: 98.3 -> 110.9)
-  const int64_t most_fused = b->shape.work_groups > 0 ? b->shape.work_groups : max_resident_blocks();
-  const int64_t resident_fused = std::min<int64_t>(
-      {(int64_t)resident_fused_blocks(b->fp64, b->maxN, false, true) * (nl > 1 ? 3 : 2) / 2, most_fused,
-       (int64_t)max_resident_blocks()});
-  const int64_t lane_fused = std::max<int64_t>(resident_fused / nl, (n + nl - 1) / nl);
-  double fused_work = 0.0;
+  // the balance gives: 98.3 -> 110.9, unless there are few workgroups a case and much
+  // for each: 300 discharges of 50k + 50k 219 -> 169, 256 of 60k + 60k 209 -> 203, of 20k
+  // + 20k 71 -> 76; in FP64 256 of 20k + 20k 179 -> 125)
+  double fused_work = 0.0, particles = 0.0, candidates = 0.0;
   bool fused = true;
   for (const pm_case* c : b->cases)
     if (c) {
       fused_work += fused_work_of(&c->prm, c->c);
+      particles += (double)(c->prm.np_e + c->prm.np_i);
+      candidates += expected_candidates(&c->prm, c->c);
       fused = fused && !c->c.prof;           // timestamps are taken of the two launches
     }
+  const int64_t wave = resident_fused_blocks(b->fp64, b->maxN, false, true);
+  fused = fused && fuse_batch(b->fp64, particles, candidates, wave);
+  const bool two = !b->slotted && ((particles > 50e3 * (double)wave && 8 * (int64_t)n > wave) || 4 * (int64_t)n >= 3 * wave);
+  const int64_t most_fused = b->shape.work_groups > 0 ? b->shape.work_groups : max_resident_blocks();
+  const int64_t resident_fused =
+      std::min<int64_t>({nl > 1 ? wave * 3 / 2 : two ? wave * 2 : wave, most_fused, (int64_t)max_resident_blocks()});
+  const int64_t lane_fused = std::max<int64_t>(resident_fused / nl, (n + nl - 1) / nl);
   std::vector<uint32_t> nb(n, 0), nm(n, 0), ns(n, 0), nf(n, 0), sw, mw, rw, fw;
   int64_t work_total = 0;
   std::vector<BatchLane> lanes(nl);
@@ -1526,9 +1564,14 @@ pm_status write_tables(pm_batch* b, hipStream_t st) {
       wt[k] = fused_work_of(&c->prm, c->c);
       lane_work += wt[k];
     }
-    const std::vector<int64_t> fg = b->slotted
-        ? shares(wt, lane_fused, ft)
-        : shares(wt, std::max<int64_t>(m, (int64_t)((double)resident_fused * lane_work / std::max(fused_work, 1.0))), ft);
+    const int64_t lane_total = b->slotted
+        ? lane_fused
+        : std::max<int64_t>(m, (int64_t)((double)resident_fused * lane_work / std::max(fused_work, 1.0)));
+    // beside other lanes the fullest workgroup's end is filled by theirs, so that
+    // plain shares do as long as a case has several (the sweep 297 ms for 4 RF periods
+    // with even ones, 295 without)
+    const std::vector<int64_t> fg =
+        nl == 1 || 4 * (int64_t)m > lane_total ? even_shares(wt, lane_total, ft) : shares(wt, lane_total, ft);
     BatchLane& L = lanes[g];
     L.maxN = b->slotted ? b->maxN : 0;
     L.fused_off = (int)fw.size();
