@@ -188,6 +188,18 @@ int resident_step_blocks(bool fp64, int N, int unroll, int waves, bool batch) {
   return per_cu * cus;
 }
 
+// Workgroups that share a case's particles in the push when the caller names no
+// number: one resident wave, but at most five on a CU.  A large case streams slower
+// through more (12M + 12M particles on 512 cells: 145 us with 1280 workgroups on 256
+// CUs, 161 with 1536, 168 with the 1792 that its registers allow; 1M + 1M 27 to 28 us
+// with any of them).
+int push_groups_for(const pm_case_params* p, int unroll, int waves) {
+  int dev = 0, cus = 0;
+  (void)hipGetDevice(&dev);
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 1;
+  return work_grid_for(p, std::min(resident_step_blocks(p->fp64, p->n_cells, unroll, waves, false), 5 * cus));
+}
+
 // Workgroups of a fused step resident on the whole device at once.
 int resident_fused_blocks(bool fp64, int N, bool flux, bool batch) {
   int dev = 0, cus = 0;
@@ -963,7 +975,7 @@ pm_status pm_init_case(const pm_case_params* p, void* arena, size_t bytes, void*
   c->warnings = warnings_of(p, c->c);
   fill_args<float>(c->af, c->c, c->arena, m);
   fill_args<double>(c->ad, c->c, c->arena, m);
-  c->work_grid = work_grid_for(p, resident_step_blocks(p->fp64, p->n_cells, c->c.unroll, c->c.waves, false));
+  c->work_grid = push_groups_for(p, c->c.unroll, c->c.waves);
   c->step_grid = std::max(c->work_grid, slot_grid_for(p));
   c->mcc_grid = mcc_grid_for(
       p, c->c, mcc_per_lane(expected_candidates(p, c->c), resident_mcc_blocks(p->fp64, p->n_cells, false)));
@@ -1175,7 +1187,7 @@ pm_status pm_set_launch_shape(pm_case* c, const pm_launch_shape* sh, void* strea
   const int most = work_grid_for(&c->prm);
   c->work_grid = sh->work_groups > 0
       ? std::min(sh->work_groups, most)
-      : work_grid_for(&c->prm, resident_step_blocks(c->prm.fp64, c->c.N, sh->unroll, sh->waves, false));
+      : push_groups_for(&c->prm, sh->unroll, sh->waves);
   c->step_grid = std::max(c->work_grid, slot_grid_for(&c->prm));
   c->fused_grid = fused_grid_for(&c->prm, c->c, sh->work_groups);
   fill_args<float>(c->af, c->c, c->arena, c->map);

@@ -87,3 +87,13 @@ def test_several_steps_keep_the_workgroup_limit(pm, kind):
     assert t_held > 3 * t_free, (t_held, t_free)
     held.set_launch_shape(work_groups=0)
     assert _time(torch, lambda: held.step(25)) < t_held / 3
+
+
+def test_default_workgroups_of_a_large_case(pm):
+    """At most five on a CU, whatever the registers allow: more of them stream slower."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    c = pm.Case(W.discharge_working())
+    for sh in (dict(), dict(unroll=8, waves=6), dict(unroll=16, waves=0)):
+        c.set_launch_shape(work_groups=0, **sh)
+        assert 256 < c.launch_shape()["work_groups"] <= 5 * cus
