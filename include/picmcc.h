@@ -435,8 +435,8 @@ typedef struct {
   int32_t work_groups;    /* workgroups that share the particles (a case: at most one   */
                           /* per 256 initial particles; a batch: over all its cases);   */
                           /* 0 = one resident wave of the device (a case: at most five  */
-                          /* per CU).  Several steps in one call use at most as many (a */
-                          /* batch at least one per case)                               */
+                          /* per CU, three in FP64).  Several steps in one call use at  */
+                          /* most as many (a batch at least one per case)               */
   int32_t deposit_mode;   /* charge into the LDS tile: 0 an atomic per particle, 1 a    */
                           /* wavefront in one cell summed by DPP, per-particle atomics */
                           /* otherwise                                                 */

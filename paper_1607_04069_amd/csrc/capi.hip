@@ -189,15 +189,16 @@ int resident_step_blocks(bool fp64, int N, int unroll, int waves, bool batch) {
 }
 
 // Workgroups that share a case's particles in the push when the caller names no
-// number: one resident wave, but at most five on a CU.  A large case streams slower
-// through more (12M + 12M particles on 512 cells: 145 us with 1280 workgroups on 256
-// CUs, 161 with 1536, 168 with the 1792 that its registers allow; 1M + 1M 27 to 28 us
-// with any of them).
+// number: one resident wave, but at most five on a CU (three in FP64).  A large case
+// streams slower through more (12M + 12M particles on 512 cells: 145 us with 1280
+// workgroups on 256 CUs, 161 with 1536, 168 with the 1792 that its registers allow; 1M
+// + 1M 27 to 28 us with any of them; in FP64 3M + 3M 77.9 us with 768, 80.4 with 1024,
+// 83.3 with 1280, though 1M + 1M 35.5, 31.8 and 32.2).
 int push_groups_for(const pm_case_params* p, int unroll, int waves) {
   int dev = 0, cus = 0;
   (void)hipGetDevice(&dev);
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 1;
-  return work_grid_for(p, std::min(resident_step_blocks(p->fp64, p->n_cells, unroll, waves, false), 5 * cus));
+  return work_grid_for(p, std::min(resident_step_blocks(p->fp64, p->n_cells, unroll, waves, false), (p->fp64 ? 3 : 5) * cus));
 }
 
 // Workgroups of a fused step resident on the whole device at once.
