@@ -861,6 +861,8 @@ pm_status tp_run(const pm_tp_params* tp, const pm_tp_source* src, char* base, ch
   const double across = tp->gap_m / (std::sqrt(2.0 * kE / m) * std::sqrt(src->u_s_ev)), k = nu_max * across;
   const double events = tp->mode == PM_TP_BOX ? (double)tp->e_max : tp->dt_s > 0 ? across / tp->dt_s : k + 2.5 * k * k;
   t.expect = (float)std::min(events, (double)tp->e_max);
+  // at the mean relative speed of a thermal atom
+  t.hit = (float)std::pow(std::sqrt(8.0 * kKB * tp->t_gas_k / (M_PI * mr)) / g_cap, 2.0 - 2.0 * tp->omega);
   t.dt = tp->dt_s;
   t.n_ebins = tp->n_ebins;
   t.n_tbins = tp->n_tbins;

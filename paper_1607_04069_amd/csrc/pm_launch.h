@@ -75,7 +75,7 @@ struct TpConst {
   int64_t e_max;
   int64_t n_atoms, first_atom;
   uint64_t seed, job;
-  float expect;              // candidate events of an atom, roughly (for the launch's shape alone)
+  float expect, hit;         // candidate events of an atom and the part that collides, roughly (for the launch's shape alone)
   int wlog, widest;          // lanes per atom at the start and at most: 2^wlog, 2^widest (set by the launcher)
   int64_t run, first_run;    // atoms a wavefront takes at a time; the first run that is no wavefront's own
 };

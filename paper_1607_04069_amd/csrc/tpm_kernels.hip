@@ -345,11 +345,17 @@ struct Queue {
 __device__ __forceinline__ int take(const TpConst& T, Queue& q, unsigned long long* next, int want, int lane,
                                     int64_t* first) {
   if (q.at >= q.end && !q.dry) {
-    unsigned long long r = 0;
-    if (lane == 0) r = atomicAdd(next, (unsigned long long)T.run);
-    r = (unsigned long long)__builtin_amdgcn_readfirstlane((int)(uint32_t)r) & 0xFFFFFFFFull |
-        (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(r >> 32)) << 32;
-    q.at = (int64_t)r + T.first_run;
+    // with every atom in some wavefront's own run there is nothing to ask for (the
+    // thousands of atomics on one address that say so took 20 us of 280, 209404 atoms
+    // at 0.06 Pa)
+    q.at = T.first_run;
+    if (T.first_run < T.n_atoms) {
+      unsigned long long r = 0;
+      if (lane == 0) r = atomicAdd(next, (unsigned long long)T.run);
+      r = (unsigned long long)__builtin_amdgcn_readfirstlane((int)(uint32_t)r) & 0xFFFFFFFFull |
+          (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(r >> 32)) << 32;
+      q.at += (int64_t)r;
+    }
     q.end = min(q.at + T.run, T.n_atoms);
     if (q.at >= T.n_atoms) {
       q.dry = true;
@@ -453,7 +459,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_tp_flight(TpConst T, TpTally* tal
         }
       }
       const uint64_t live = __ballot(alive);
-      if (q.dry && __popcll(live) <= 32 && !__ballot(alive && fresh)) break;
+      if (q.dry && __popcll(live) <= (T.widest ? 32 : 0) && !__ballot(alive && fresh)) break;
       if (alive) {
         const Uniforms8<float> U = draw_atom(T, k, fresh ? 0ull : (uint64_t)a.e,
                                              fresh ? rng_tag(SP_AL, PU_TP_SRC) : rng_tag(SP_AL, PU_TP_EVT));
@@ -507,7 +513,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_tp_flight(TpConst T, TpTally* tal
 
   // 2^wlog lanes per atom; every variable of the atom is the same in its lanes.
   // A gridless atom with 16 lanes (a row) keeps a row of drawn events and walks
-  // through it, pos the next one, stop by stop; the flights it made on the way
+  // through it (in the box its place does not matter and is not wrapped), pos the next one, stop by stop; the flights it made on the way
   // (xa -> xb at va, one per lane) are tallied together when the row is used up.
   EventDraw D = {};
   int pos = 16;
@@ -558,7 +564,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_tp_flight(TpConst T, TpTally* tal
       wlog = to;
       continue;
     }
-    if (!kFixed && wlog == 4 && T.mode == 0) {
+    if (!kFixed && wlog == 4) {
       if (__ballot(alive && pos >= 16)) {
         // a row of 16 draws: everything of these events that the atom's state does not enter
         if (flown && T.n_xbins) track_tally(T, S, xa, xb, va);
@@ -575,7 +581,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_tp_flight(TpConst T, TpTally* tal
         float x = a.x, t = a.t;
         row_chain(a.vx, tj, i, x, t);
         const float xn = fmaf(a.vx, D.tau, x);
-        const bool open = i >= pos, out = !(xn >= 0.0f && xn < T.f.L);
+        const bool open = i >= pos, out = T.mode == 0 && !(xn >= 0.0f && xn < T.f.L);
         const Partner p = meet<false>(T, D, a);
         const bool hit = !out && D.u5 < p.ratio;
         const bool last = !out && (uint64_t)e + 1 >= (uint64_t)T.e_max;
@@ -862,18 +868,29 @@ static int compute_units() {
 // atom, 60 with one; 60 steps of 50021 in the periodic box 161 us with 16, 130 with
 // four).  A fixed step at which many tests succeed has little to look ahead for: its
 // lanes stay below 16 over the probability at the majorant (at 1.6, 10247 atoms 4.1 ms
-// with 64 lanes and 2.6 with 8; at 0.16 5.5 with 64 and 6.1 with 32).
+// with 64 lanes and 2.6 with 8; at 0.16 5.5 with 64 and 6.1 with 32), and of a flight of
+// fewer than 64 steps stricter (35 steps of 53405 atoms at 0.6 172 us with four, 132
+// with one; 6000 of them 101 and 117).  The same holds for
+// a gridless flight in the box, whose atoms all end at the event limit and so leave
+// nobody to wait for, and for one that a low limit ends: the more atoms, the fewer of
+// their collisions pay for lanes (2000 events in the box, omega 0.99, 53k atoms 5.3 ms
+// with four lanes, 2.3 with one; omega 0.55 1.5 and 2.2; 6000 atoms at 0.9 1.3 with 16 and
+// 2.2).
 hipError_t launch_tp_flight(TpConst T, TpTally* tally, uint64_t* e_hist, uint64_t* th_hist, uint64_t* tof_hist,
                             TpTrace trace, int64_t* prof, hipStream_t st) {
   const int64_t most = (int64_t)compute_units() * 4 * 4;
   const bool fixed = T.dt > 0.0;
   T.widest = fixed ? kWidest<true> : kWidest<false>;
-  while (T.widest > 1 && T.f.nu_dt * (float)(1 << T.widest) > 16.0f) --T.widest;
+  const bool brief = fixed && T.e_max < 64;
+  while (T.widest > 1 && T.f.nu_dt * (float)(1 << T.widest) > (brief ? 2.0f : 16.0f)) --T.widest;
   T.wlog = 0;
-  if (T.expect >= 1.0f)
-    while (T.wlog < T.widest && T.n_atoms <= (fixed ? 128 : 64) * most >> (T.wlog + 1) &&
+  const bool alone = !fixed && (((T.mode != 0 || T.e_max < 1024) && (float)T.n_atoms * T.hit > 2.0f * (float)most) ||
+                                (T.mode != 0 && T.e_max < 128 && T.hit > 0.6f));
+  if (T.expect >= 1.0f && !alone)
+    while (T.wlog < T.widest && T.n_atoms <= (brief ? 8 : fixed ? 128 : 64) * most >> (T.wlog + 1) &&
            (int64_t)8 << (T.wlog + 1) <= T.e_max)
       ++T.wlog;
+  if (alone && T.mode != 0) T.widest = 0;
   const int64_t per_wave = 64 >> T.wlog;
   const int64_t waves = std::min((T.n_atoms + per_wave - 1) / per_wave, most);
   const int grid = (int)std::max<int64_t>(1, (waves + kBlock / 64 - 1) / (kBlock / 64));

@@ -34,3 +34,19 @@ def test_short_and_dense_flights_do_not_change_an_atom(pm, kw):
         for k, v in small["trace"].items():
             assert np.array_equal(v, big[k][first:first + n], equal_nan=v.dtype.kind == "f"), (n, k)
         assert small["n_target"] == int((small["trace"]["wall"] == 0).sum())
+
+
+# the box and low event limits with few and with many collisions an event: one lane, 16 and between
+@pytest.mark.parametrize("omega", [0.55, 0.99])
+@pytest.mark.parametrize("kw", [dict(mode=1, e_max=150), dict(mode=1, e_max=40), dict(mode=0, e_max=150),
+                                dict(mode=1, e_max=300, dt_s=1e-6)])
+def test_boxes_and_limits_do_not_change_an_atom(pm, kw, omega):
+    def flight(n, first=0):
+        src, tp = _inputs(n, first, p_pa=3.0, **kw)
+        return pm.run_test_particles(src, dict(tp, omega=omega), trace=True)
+    big = flight(N_ONE_LANE)["trace"]
+    for n, first in ((1, 5), (63, 100), (4097, 1000), (16_500, 3), (33_000, 70_000), (66_000, 30_001)):
+        small = flight(n, first)
+        for k, v in small["trace"].items():
+            assert np.array_equal(v, big[k][first:first + n], equal_nan=v.dtype.kind == "f"), (n, k)
+        assert small["events"] == int(small["trace"]["events"].astype(np.int64).sum())
