@@ -785,7 +785,7 @@ struct TpLayout {
 };
 
 // The most that a flight's results are read back in one copy.
-constexpr size_t kTpReadBytes = 64 * 1024;
+constexpr size_t kTpReadBytes = 128 * 1024;
 
 TpLayout tp_layout(const pm_tp_params* tp) {
   Layout L;
